@@ -57,37 +57,50 @@ struct Task {
 //    i % R, so one group's K/V tiles are shared through those XCDs' L2;
 //  - within an XCD, query-block rows run heaviest first (i descending) with
 //    the query heads of the group adjacent (they read the same K/V).
-// Shapes that do not fit this scheme use the plain heaviest-first order.
-struct TaskMap {
-  int batch, heads_q, heads_kv, nb;
-  int R;    // XCDs per group; 0 selects the plain order
-  int gpp;  // groups per phase (R * gpp == 8)
-  int tpp;  // tasks per XCD per phase = (nb / R) * G
+// Where gpp does not divide the groups or R the blocks, the phases are rounded
+// up and the workgroups without a task end at once.  Each phase starts
+// its residues one XCD further, so that many phases of few blocks use every XCD.  Measured at 50001
+// tokens (782 blocks, 32 query / 8 KV heads, TopK 0.15): 4.72 ms when such
+// counts ran every head's rows interleaved over all XCDs, 3.5 ms in this order.
+// (The launch's first instructions are this decode, alone on its critical path:
+// its divisions multiply by reciprocals formed on the host.)
+struct Divisor {
+  uint32_t d, m;  // m = floor(2^32 / d), capped at 2^32 - 1
 };
 
-__device__ __forceinline__ Task decode_task(const TaskMap& m, int wg) {
-  const int G = m.heads_q / m.heads_kv;
+// u / d for u < 2^31: the product is at most one below the quotient.
+__device__ __forceinline__ int divide(const Divisor& v, int u) {
+  const uint32_t q = __umulhi((uint32_t)u, v.m);
+  return (int)((uint32_t)u - q * v.d >= v.d ? q + 1 : q);
+}
+
+struct TaskMap {
+  int groups, nb;  // groups = batch * heads_kv
+  int rsh;         // log2 of the XCDs per group, R
+  int gpp;         // groups per phase (R * gpp == 8)
+  int total;       // workgroups of all phases
+  Divisor hkv;     // KV heads
+  Divisor G;       // query heads per group
+  Divisor tpp;     // tasks per XCD per phase = ceil(nb / R) * G
+};
+
+// A workgroup without a task decodes to row 0 of an existing head with `none`
+// set: it may read its task's inputs before it ends.
+__device__ __forceinline__ Task decode_task(const TaskMap& m, int wg, bool& none) {
   Task t;
-  if (m.R > 0) {
-    const int x = wg % 8;
-    const int u = wg / 8;
-    const int ph = u / m.tpp;
-    const int rem = u % m.tpp;
-    const int nu = rem / G;
-    const int hh = rem % G;
-    const int slot = ph * m.gpp + x / m.R;
-    const int rho = x % m.R;
-    t.i = m.nb - 1 - (nu * m.R + rho);
-    t.b = slot / m.heads_kv;
-    t.h = (slot % m.heads_kv) * G + hh;
-  } else {
-    const int bh = m.batch * m.heads_q;
-    const int nu = wg / bh;
-    const int rem = wg % bh;
-    t.b = rem / m.heads_q;
-    t.h = rem % m.heads_q;
-    t.i = m.nb - 1 - nu;
-  }
+  const int x = wg & 7;
+  const int u = wg >> 3;
+  const int ph = divide(m.tpp, u);
+  const int rem = u - ph * (int)m.tpp.d;
+  const int nu = divide(m.G, rem);
+  const int hh = rem - nu * (int)m.G.d;
+  const int slot = ph * m.gpp + (x >> m.rsh);
+  const int rho = (x + ph) & ((1 << m.rsh) - 1);
+  const int i = m.nb - 1 - ((nu << m.rsh) + rho);
+  none = slot >= m.groups || i < 0;
+  t.i = max(i, 0);
+  t.b = divide(m.hkv, min(slot, m.groups - 1));
+  t.h = (min(slot, m.groups - 1) - t.b * (int)m.hkv.d) * (int)m.G.d + hh;
   t.p = 0;
   return t;
 }
@@ -573,11 +586,12 @@ void attn_fwd_bf16_kernel(KernelArgs ka) {
   bool prefetched = false;
   for (;;) {  // SPLIT: tasks drawn from the queue; otherwise a single pass
   Task t;
+  bool none = false;
   if constexpr (SPLIT) {
     if (prefetched) t = t_next;
     else if (!next_split_task(t)) break;
   } else {
-    t = decode_task(ka.map, blockIdx.x + ka.task_base);
+    t = decode_task(ka.map, blockIdx.x + ka.task_base, none);
   }
   const bool pre = SPLIT && prefetched;
   const int tid = threadIdx.x;
@@ -650,6 +664,7 @@ void attn_fwd_bf16_kernel(KernelArgs ka) {
 
   // row list
   const RowList<SPARSE> list = make_list<SPARSE, SPLIT>(a, t);
+  if (none) return;  // (here rather than above, which would hold every argument's load back until the decode is done)
   const bool pool = !SPARSE && !SPLIT && a.gt != nullptr;  // ground-truth mode
   const int64_t trow = ((int64_t)t.b * a.heads_q + hq) * a.n_blocks + t.i;  // this wavefront's head
   float* const rrow = pool ? a.pool_r + trow * a.n_blocks * 64 : nullptr;
@@ -1104,7 +1119,9 @@ __global__ __launch_bounds__(128) void attn_fwd_f32_kernel(KernelArgs ka, int sp
   __shared__ __attribute__((aligned(16))) float sL2[64];
 
   const AttnArgs& a = ka.a;
-  const Task t = decode_task(ka.map, blockIdx.x);
+  bool none;
+  const Task t = decode_task(ka.map, blockIdx.x, none);
+  if (none) return;
   const int tid = threadIdx.x;
   const int wave = tid / 64;
   const int lane = tid % 64;
@@ -1302,8 +1319,9 @@ __global__ __launch_bounds__(256) void split_bounds_kernel(AttnArgs a) {
   }
 }
 
-// Groups per phase: the largest power of two whose K + V stay within 32 MiB;
-// each group is then spread over R = 8 / gpp XCDs.  Measured at 131072 tokens
+// Groups per phase: the power of two whose K + V stay within 32 MiB and whose
+// rounded-up phases hold the fewest workgroups, the largest of those; each
+// group is then spread over R = 8 / gpp XCDs.  Measured at 131072 tokens
 // (64 MiB of K + V per group): one group at a time over all 8 XCDs beat one
 // group per XCD by 11% (sparse) and 7% (dense).  At 65536 tokens with 7 query
 // heads per KV group and per-head densities of 5-40% (32 MiB per group), one
@@ -1311,32 +1329,39 @@ __global__ __launch_bounds__(256) void split_bounds_kernel(AttnArgs a) {
 // groups' unequal work no longer leaves half the XCDs idle at the end; 8k and
 // 32k shapes (4 and 16 MiB per group) ran the same with budgets of 32 and 64 MiB,
 // and slower with 16 or less.
-#ifndef SEER_KV_PHASE_BUDGET_MB
-#define SEER_KV_PHASE_BUDGET_MB 32
-#endif
+constexpr double kPhaseBudget = 32.0 * 1024.0 * 1024.0;
+
+static Divisor divisor(int d) {
+  return Divisor{(uint32_t)d, (uint32_t)std::min<uint64_t>((1ull << 32) / (uint32_t)d, 0xFFFFFFFFull)};
+}
+
 static TaskMap make_map(const AttnArgs& a) {
   TaskMap m;
-  m.batch = a.batch;
-  m.heads_q = a.heads_q;
-  m.heads_kv = a.heads_kv;
+  m.groups = a.batch * a.heads_kv;
   m.nb = a.n_blocks;
-  m.R = 0;
-  m.gpp = 0;
-  m.tpp = 0;
-  const int slices = a.batch * a.heads_kv;
   const int G = a.heads_q / a.heads_kv;
+  m.hkv = divisor(a.heads_kv);
+  m.G = divisor(G);
   const double kv_bytes = 2.0 * a.n_blocks * 64.0 * a.head_dim * (a.bf16 ? 2 : 4);
-  const double budget = SEER_KV_PHASE_BUDGET_MB * 1024.0 * 1024.0;
-  for (int gpp = 8; gpp >= 1; gpp /= 2) {
-    const int R = 8 / gpp;
-    if (slices % gpp != 0 || a.n_blocks % R != 0) continue;
-    if (gpp > 1 && gpp * kv_bytes > budget) continue;
-    m.R = R;
+  int64_t fewest = INT64_MAX;
+  for (int rsh = 0; rsh <= 3; ++rsh) {
+    const int gpp = 8 >> rsh, R = 1 << rsh;
+    if (gpp > 1 && gpp * kv_bytes > kPhaseBudget) continue;
+    const int tpp = ((a.n_blocks + R - 1) / R) * G;
+    const int64_t total = (int64_t)((m.groups + gpp - 1) / gpp) * 8 * tpp;
+    if (total >= fewest) continue;
+    fewest = total;
+    m.rsh = rsh;
     m.gpp = gpp;
-    m.tpp = (a.n_blocks / R) * G;
-    break;
+    m.tpp = divisor(tpp);
+    m.total = (int)total;
   }
   return m;
+}
+
+// Whether a phase holds a single group because its K and V fill the budget.
+static bool group_fills_phase(const AttnArgs& a) {
+  return make_map(a).gpp == 1 && 4.0 * a.n_blocks * 64.0 * a.head_dim * (a.bf16 ? 2 : 4) > kPhaseBudget;
 }
 
 }  // namespace
@@ -1417,7 +1442,7 @@ static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count);
 // 8 launches 17.8 ms, one launch 18.1 ms.  Not for the split or pooling modes.
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s, int* count) {
   const int groups = a.batch * a.heads_kv;
-  if (a.split_w > 0 || a.gt != nullptr || groups <= 1 || make_map(a).gpp != 1)
+  if (a.split_w > 0 || a.gt != nullptr || groups <= 1 || !group_fills_phase(a))
     return launch_attn_one(a, s, count);
   const int G = a.heads_q / a.heads_kv;
   const int64_t es = a.bf16 ? 2 : 4;
@@ -1515,7 +1540,7 @@ static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count) 
     AttnArgs v = a;
     v.heads_q = a.heads_q / nh;
     ka.map = make_map(v);
-    const int64_t total = (int64_t)a.batch * v.heads_q * a.n_blocks;
+    const int64_t total = ka.map.total;
     if (total == 0) return hipSuccess;
     ka.split = SplitMap{a.heads_q, a.heads_kv, a.n_blocks, 0, 0, 0, 0, 1};
     ka.scale_log2 = a.scale * kLog2e;
@@ -1540,7 +1565,7 @@ static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count) 
   }
   ka.scale_log2 = a.scale * kLog2e;
   ka.task_base = 0;
-  const int64_t total = (int64_t)a.batch * a.heads_q * a.n_blocks;
+  const int64_t total = ka.map.total;
   if (total == 0) return hipSuccess;
   dim3 grid((unsigned)total), block(128);
   const bool sparse = a.count != nullptr;

@@ -1,0 +1,42 @@
+"""The attention task order covers every (batch, head, query block) row exactly
+where the row count or the group count does not divide the order's phases: each
+call equals, bit for bit, the calls on its (batch, KV head) groups one by one
+(whose phases differ), into outputs filled with NaN beforehand."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+seer = pytest.importorskip("paper_2410_13276_amd")
+
+
+# 1 and 2 blocks with odd group counts (phases rounded up over groups), block counts around 8, and K + V beyond
+# the 32 MiB of a phase (261 and 523 blocks: 4 and 2 groups per phase at 8 groups; 1021: one launch per group)
+@pytest.mark.parametrize("B,Hq,Hkv,seq", [(1, 1, 1, 1), (9, 2, 1, 100), (3, 6, 3, 64), (5, 3, 3, 449), (1, 4, 2, 577),
+                                          (2, 14, 2, 1001), (1, 16, 8, 16700), (1, 8, 8, 33409), (1, 4, 2, 65300)])
+def test_every_row_once(B, Hq, Hkv, seq):
+    print(f"[task order] {B} {Hq}/{Hkv} {seq}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(seq)
+    q, k, v = (torch.randn(B, h, seq, 128, generator=gen, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    nb, G = -(-seq // 64), Hq // Hkv
+    i = torch.arange(nb, device="cuda")
+    keep = torch.rand(B, Hq, nb, nb, generator=gen, device="cuda") < 4.0 / nb
+    dense = ((keep | (i[None, :] == i[:, None])) & (i[None, :] <= i[:, None])).to(torch.uint8)
+    mask = seer.mask_from_dense(dense, heads_kv=Hkv)
+    o = torch.full_like(q, float("nan"))
+    lse = torch.full((B, Hq, seq), float("nan"), device="cuda")
+    seer.bsattn(q, k, v, mask, out=o, lse=lse)
+    od = torch.full_like(q, float("nan"))
+    if nb <= 300:
+        seer.dense_attn(q, k, v, out=od)
+    for b in range(B):
+        for g in range(Hkv):
+            hs = slice(g * G, g * G + G)
+            qs, ks, vs = q[b:b + 1, hs], k[b:b + 1, g:g + 1], v[b:b + 1, g:g + 1]
+            m = seer.BlockMask(count=mask.count[b:b + 1, hs].contiguous(), idx=mask.idx[b:b + 1, hs].contiguous())
+            o1, l1 = seer.bsattn(qs, ks, vs, m, out=torch.empty_like(qs).contiguous(), want_lse=True)
+            assert torch.equal(o[b:b + 1, hs].view(torch.int16), o1.view(torch.int16))
+            assert torch.equal(lse[b:b + 1, hs], l1)
+            if nb <= 300:
+                od1, _ = seer.dense_attn(qs, ks, vs, out=torch.empty_like(qs).contiguous())
+                assert torch.equal(od[b:b + 1, hs].view(torch.int16), od1.view(torch.int16))
