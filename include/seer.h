@@ -394,10 +394,11 @@ seer_status seer_gate_distill(const seer_attn_desc* desc, const seer_gate_desc* 
  * from desc: q_stride[2] is the token stride and q_stride[1] the head stride
  * (q_stride[0] is ignored), e.g. [T][H][D] packing.  Every sequence is its own
  * causal (or non-causal) problem: no attention or pooling crosses a boundary,
- * and each has nb_b = ceil(len_b / block) blocks.  The calls run one batch-1
- * pass per sequence on `stream`, through the same kernels as seer_gate /
- * seer_bsattn (so results equal separate per-sequence calls bit for bit);
- * arguments of every sequence are validated before anything is launched.
+ * and each has nb_b = ceil(len_b / block) blocks.  Short sequences share their
+ * launches (up to 64 of them each), longer ones run one batch-1 pass each on
+ * `stream`; either way a row's arithmetic is that of seer_gate / seer_bsattn (so
+ * results equal separate per-sequence calls bit for bit); arguments of every
+ * sequence are validated before anything is launched.
  *
  * Mask layout: the sequences' row sets back to back.  Sequence b's count rows
  * [H][nb_b] start at element sum_{b'<b} H nb_b' of mask->count, and its idx
@@ -412,13 +413,16 @@ seer_status seer_gate_distill(const seer_attn_desc* desc, const seer_gate_desc* 
 size_t seer_varlen_mask_elems(const seer_attn_desc* desc, const int32_t* cu_seqlens_host, int32_t block,
                               int32_t kv_shared, size_t* count_elems);
 
-/* Workspace bytes of seer_gate_varlen: the largest sequence's seer_gate workspace
- * with the logits in the workspace (0 on invalid arguments). */
+/* Workspace bytes of seer_gate_varlen (0 on invalid arguments): the largest
+ * sequence's seer_gate workspace with the logits in the workspace, or the
+ * projected rows of all short sequences up to 64 MiB, whichever is larger.  The
+ * call needs the former; with less than the latter its shared launches serve
+ * fewer sequences at a time. */
 size_t seer_gate_varlen_workspace_bytes(const seer_attn_desc* desc, const int32_t* cu_seqlens_host,
                                         const seer_gate_desc* gate);
 
 /* seer_gate over every sequence of a packed batch (section 3.1, Eq. 1, Eq. 3 / 4
- * per sequence); the workspace is reused by the sequences in stream order. */
+ * per sequence); the workspace is reused by the launches in stream order. */
 seer_status seer_gate_varlen(const seer_attn_desc* desc, const int32_t* cu_seqlens_host,
                              const seer_gate_desc* gate, const void* q, const void* k, const float* wq,
                              const float* wk, seer_block_mask* out, void* workspace, size_t workspace_bytes,

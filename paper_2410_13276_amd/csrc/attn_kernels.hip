@@ -161,6 +161,47 @@ struct KernelArgs {
   int task_base;     // first task of this launch (launches in batches, see launch_attn_one)
 };
 
+// A launch over several sequences of a packed batch carries their table.
+template <bool VAR>
+struct LaunchArgs : KernelArgs {};
+template <>
+struct LaunchArgs<true> : KernelArgs {
+  PackedSeqs seqs;
+};
+
+// Task of a packed launch and its sequence's view of the packed tensors and
+// mask.  The sequences follow each other longest first, each with its rows
+// heaviest first, every row's heads together with the KV heads fastest (with 8
+// of them each XCD keeps to one), so that short rows come last over the whole
+// launch.  map.hkv counts the KV heads, map.G the head slots per KV head.
+__device__ __forceinline__ Task decode_packed(const KernelArgs& ka, const PackedSeqs& p, int wg, AttnArgs& a) {
+  const int s = packed_find(p.first, p.n, wg);
+  const int slots = (int)(ka.map.hkv.d * ka.map.G.d);
+  const int len = p.len[s];
+  const int64_t t0 = p.tok0[s];
+  a = ka.a;
+  a.seq_len = len;
+  a.n_blocks = (len + 63) / 64;
+  a.mask_blocks = a.mask_shift ? (len + 127) / 128 : a.n_blocks;
+  a.q.ptr = static_cast<const uint16_t*>(a.q.ptr) + t0 * a.q.ss;
+  a.k.ptr = static_cast<const uint16_t*>(a.k.ptr) + t0 * a.k.ss;
+  a.v.ptr = static_cast<const uint16_t*>(a.v.ptr) + t0 * a.v.ss;
+  a.o = static_cast<uint16_t*>(a.o) + t0 * a.oss;
+  if (a.lse) a.lse += t0 * a.heads_q;
+  const int64_t mh = a.mask_kv ? a.heads_kv : a.heads_q;
+  a.count += mh * p.mrow[s];
+  a.idx += mh * p.midx[s];
+  const int r = wg - p.first[s];
+  const int lev = r / slots, slot = r - lev * slots;
+  Task t;
+  t.b = 0;
+  t.p = 0;
+  t.i = a.n_blocks - 1 - lev;
+  const int hh = divide(ka.map.hkv, slot);
+  t.h = (slot - hh * (int)ka.map.hkv.d) * (int)ka.map.G.d + hh;
+  return t;
+}
+
 // Iterates the active key blocks of a row: the compacted list for the sparse
 // kernel, 0..i (causal) or 0..nb-1 for the dense one.  Entries that are out of
 // range (>= nb, or > i when causal) end the row.
@@ -539,9 +580,11 @@ constexpr int kListWhole = 2048;
 // wavefronts each, for the same query block; each K/V tile is loaded once into
 // LDS for all of them, which divides the K/V loads by NH.  The task map then
 // counts head slots of NH heads.
-template <int D, bool SPARSE, bool SPLIT, bool RAGGED, int NH = 1>
+//
+// VAR: the rows of several sequences of a packed batch (decode_packed).
+template <int D, bool SPARSE, bool SPLIT, bool RAGGED, int NH = 1, bool VAR = false>
 __global__ __launch_bounds__(128 * NH) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_fwd_bf16_kernel(KernelArgs ka) {
+void attn_fwd_bf16_kernel(LaunchArgs<VAR> ka) {
   using Lay = Bf16Layout<D>;
   constexpr int NW = 2 * NH;  // wavefronts
   static_assert(NH == 1 || !SPLIT, "shared-row workgroups serve unsplit rows");
@@ -557,7 +600,11 @@ void attn_fwd_bf16_kernel(KernelArgs ka) {
   __shared__ int sLast;    // SPLIT: this task completed its row
   __shared__ int sTicket;  // SPLIT: the workgroup's next ticket of its queue
 
-  const AttnArgs& a = ka.a;
+  static_assert(!VAR || (SPARSE && RAGGED && !SPLIT), "packed launches serve unsplit sparse rows of any length");
+  AttnArgs seq_a;
+  Task seq_t;
+  if constexpr (VAR) seq_t = decode_packed(ka, ka.seqs, blockIdx.x, seq_a);
+  const AttnArgs& a = VAR ? seq_a : ka.a;
   const int queue = SPLIT ? (int)(blockIdx.x % ka.split.nq) : 0;
   if constexpr (SPLIT) {
     if (threadIdx.x == 0) sTicket = __hip_atomic_fetch_add(a.split_tickets + queue, 1, __ATOMIC_RELAXED,
@@ -590,6 +637,8 @@ void attn_fwd_bf16_kernel(KernelArgs ka) {
   if constexpr (SPLIT) {
     if (prefetched) t = t_next;
     else if (!next_split_task(t)) break;
+  } else if constexpr (VAR) {
+    t = seq_t;
   } else {
     t = decode_task(ka.map, blockIdx.x + ka.task_base, none);
   }
@@ -1111,7 +1160,7 @@ void attn_fwd_bf16_kernel(KernelArgs ka) {
 // ---------------------------------------------------------------------------
 
 template <int D>
-__global__ __launch_bounds__(128) void attn_fwd_f32_kernel(KernelArgs ka, int sparse) {
+__global__ __launch_bounds__(128) void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
   constexpr int KS = D + 4;  // LDS row stride of K (floats)
   constexpr int VS = D;      // LDS row stride of V (floats)
   __shared__ __attribute__((aligned(16))) float sK[64 * KS];
@@ -1418,7 +1467,7 @@ static int resident_capacity(const void* fn, int threads) {
   } while (0)
 
 template <int D, bool RAGGED>
-static hipError_t launch_split(const KernelArgs& ka, bool sparse, hipStream_t s, int* count) {
+static hipError_t launch_split(const LaunchArgs<false>& ka, bool sparse, hipStream_t s, int* count) {
   const AttnArgs& a = ka.a;
   const int64_t rows = (int64_t)a.batch * a.heads_q * a.n_blocks;
   if (!count) hipLaunchKernelGGL(split_bounds_kernel<D>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, a);
@@ -1427,7 +1476,7 @@ static hipError_t launch_split(const KernelArgs& ka, bool sparse, hipStream_t s,
   int64_t grid = resident_capacity(fn, 128);
   if (grid <= 0) grid = 1024;
   grid = std::min<int64_t>(grid, ka.split.total);
-  KernelArgs kq = ka;
+  LaunchArgs<false> kq = ka;
   kq.split.nq = (int)std::min<int64_t>(8, grid);
   if (sparse) SEER_LAUNCH((attn_fwd_bf16_kernel<D, true, true, RAGGED>), dim3((unsigned)grid), dim3(128), s, count, kq);
   else SEER_LAUNCH((attn_fwd_bf16_kernel<D, false, true, RAGGED>), dim3((unsigned)grid), dim3(128), s, count, kq);
@@ -1488,13 +1537,13 @@ static int kv_heads_per_wg(const AttnArgs& a) {
 }
 
 template <int D, bool SPARSE, bool RAGGED>
-static void launch_nh(const KernelArgs& ka, int nh, dim3 grid, hipStream_t s, int* count) {
+static void launch_nh(const LaunchArgs<false>& ka, int nh, dim3 grid, hipStream_t s, int* count) {
   if (nh == 4) SEER_LAUNCH((attn_fwd_bf16_kernel<D, SPARSE, false, RAGGED, 4>), grid, dim3(512), s, count, ka);
   else SEER_LAUNCH((attn_fwd_bf16_kernel<D, SPARSE, false, RAGGED, 2>), grid, dim3(256), s, count, ka);
 }
 
 template <int D>
-static void launch_nh_d(const KernelArgs& ka, int nh, bool sparse, bool ragged, dim3 grid, hipStream_t s,
+static void launch_nh_d(const LaunchArgs<false>& ka, int nh, bool sparse, bool ragged, dim3 grid, hipStream_t s,
                         int* count) {
   if (sparse) {
     if (ragged) launch_nh<D, true, true>(ka, nh, grid, s, count);
@@ -1532,7 +1581,7 @@ static int batch_size(const AttnArgs& a, bool ragged) {
 }
 
 static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count) {
-  KernelArgs ka;
+  LaunchArgs<false> ka;
   ka.a = a;
   const int nh = kv_heads_per_wg(a);
   const auto done = [&]() { return count ? hipSuccess : hipGetLastError(); };
@@ -1634,6 +1683,47 @@ static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count) 
     else return hipErrorInvalidValue;
   }
   return done();
+}
+
+// A sequence joins the packed launch while the K and V of its KV heads fit the
+// phase budget (8192 tokens at 8 KV heads of 128): alone, such a sequence runs
+// one launch over all its heads, which leaves most of the GPU idle; a longer
+// one fills it and keeps its own launches and their order.
+bool attn_packs(const AttnArgs& a, int n_blocks) {
+  return a.bf16 && a.count != nullptr && 4.0 * a.heads_kv * n_blocks * 64.0 * a.head_dim <= kPhaseBudget;
+}
+
+hipError_t launch_attn_packed(const AttnArgs& a, const PackedSeqs& seqs, hipStream_t s) {
+  if (seqs.n < 1 || seqs.n > kPackMax || !a.bf16 || !a.count || a.batch != 1) return hipErrorInvalidValue;
+  LaunchArgs<true> ka;
+  ka.a = a;
+  ka.seqs = seqs;
+  const int nh = kv_heads_per_wg(a);
+  const int slots = a.heads_q / nh;
+  ka.map = TaskMap{};
+  ka.map.hkv = divisor(a.heads_kv);
+  ka.map.G = divisor(slots / a.heads_kv);
+  ka.split = SplitMap{a.heads_q, a.heads_kv, 0, 0, 0, 0, 0, 1};
+  ka.scale_log2 = a.scale * kLog2e;
+  ka.task_base = 0;
+  int64_t total = 0;
+  for (int i = 0; i < seqs.n; ++i) {
+    if (seqs.len[i] < 1) return hipErrorInvalidValue;
+    ka.seqs.first[i] = (int)total;
+    total += (int64_t)((seqs.len[i] + 63) / 64) * slots;
+  }
+  if (total > INT32_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)total), block(128 * nh);
+  if (a.head_dim == 128) {
+    if (nh == 2) hipLaunchKernelGGL((attn_fwd_bf16_kernel<128, true, false, true, 2, true>), grid, block, 0, s, ka);
+    else hipLaunchKernelGGL((attn_fwd_bf16_kernel<128, true, false, true, 1, true>), grid, block, 0, s, ka);
+  } else if (a.head_dim == 64) {
+    if (nh == 2) hipLaunchKernelGGL((attn_fwd_bf16_kernel<64, true, false, true, 2, true>), grid, block, 0, s, ka);
+    else hipLaunchKernelGGL((attn_fwd_bf16_kernel<64, true, false, true, 1, true>), grid, block, 0, s, ka);
+  } else {
+    return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace seer

@@ -28,6 +28,14 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
 }
 
+// Index of the last of n <= 64 ascending starts that is at most x (starts[0] <=
+// x), one start per lane.  Uniform.
+__device__ __forceinline__ int packed_find(const int* starts, int n, int x) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const bool le = lane < n && starts[min(lane, n - 1)] <= x;
+  return __builtin_amdgcn_readfirstlane((int)__popcll(__ballot(le)) - 1);
+}
+
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));

@@ -99,7 +99,7 @@ struct PoolTiling {
 };
 
 template <typename T, int D, int DG, bool IS_K, int BLK, int RS>
-__device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t ss, int nb, int seq_len,
+__device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t ss, int chunk, int nb, int seq_len,
                                                const float* __restrict__ W,
                                                float* __restrict__ out, float* smem,
                                                float* srot, double rope_base,
@@ -117,7 +117,7 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
   const int c = t % TPR;
   const int rs = (t / TPR) % RS;  // this thread's row range
   const int r = t / (TPR * RS);
-  const int blk = blockIdx.x * R + r;
+  const int blk = chunk * R + r;
 
   if (blk < nb) {
     float sum[EPL], mx[EPL], mn[EPL];
@@ -174,7 +174,7 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
     // minima, and the sums divided by the block's row count
     for (int idx = t; idx < R * WIDTH; idx += 256) {
       const int rr = idx / WIDTH, col = idx % WIDTH;
-      const int bb = blockIdx.x * R + rr;
+      const int bb = chunk * R + rr;
       if (bb >= nb) continue;
       float* p = smem + rr * PSTR + col;
       float v = p[0];
@@ -224,7 +224,7 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
       const int rr = r0 + q * RSTEP;
-      const int bb = blockIdx.x * R + rr;
+      const int bb = chunk * R + rr;
       const double ang = (double)bb * w;
       const float cs = (float)cos(ang), sn = (float)sin(ang);
       const float a = srot[rr * DG + d], b = srot[rr * DG + d + HALF];
@@ -233,7 +233,7 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
   }
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
-    const int bb = blockIdx.x * R + r0 + q * RSTEP;
+    const int bb = chunk * R + r0 + q * RSTEP;
     if (bb < nb) {
       if (out) out[(int64_t)bb * DG + j] = acc[q];
       if (split) store_split(split, bb, j, DG, acc[q]);
@@ -241,32 +241,53 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
   }
 }
 
+// One workgroup's chunk of R blocks of one head: `slot` counts the heads, chunk
+// the R-block chunks of a sequence of nb blocks; row0: scratch rows per head
+// before the sequence (batch * nb, or the rows of the packed sequences before it).
 template <typename T, int D, int DG, int BLK, int RS>
-__global__ __launch_bounds__(256) void pool_proj_kernel(PoolProjArgs a) {
+__device__ __forceinline__ void pool_proj_chunk(const PoolProjArgs& a, const T* q, const T* k, int64_t row0, int chunk,
+                                                int nb, int seq_len) {
   constexpr int R = PoolTiling<T, D, DG, RS>::R;
   __shared__ __attribute__((aligned(16))) float smem[R * RS * 3 * D];
   __shared__ float srot[R * DG];
-  const int b = blockIdx.z;
   // the K heads' workgroups (max | min | avg pooling, a GEMV three times as
   // wide) are dispatched first, so that the lighter Q heads' fill the end
   const int slot = (blockIdx.y + a.heads_q) % (a.heads_q + a.heads_kv);
   if (slot < a.heads_q) {
     const int h = slot;
-    const T* x = static_cast<const T*>(a.q.ptr) + b * a.q.sb + h * a.q.sh;
-    float* out = a.qg ? a.qg + ((int64_t)b * a.heads_q + h) * a.n_blocks * DG : nullptr;
-    float* po = a.qp ? a.qp + ((int64_t)b * a.heads_q + h) * a.n_blocks * D : nullptr;
-    uint16_t* sp = a.qs ? a.qs + ((int64_t)b * a.heads_q + h) * split_rows(a.n_blocks) * 3 * DG : nullptr;
-    pool_proj_head<T, D, DG, false, BLK, RS>(x, a.q.ss, a.n_blocks, a.seq_len, a.wq + h * a.wq_head_stride, out, smem, srot,
-                                    a.rope_base, po, sp);
+    const int64_t row = row0 * a.heads_q + (int64_t)h * nb;
+    float* out = a.qg ? a.qg + row * DG : nullptr;
+    float* po = a.qp ? a.qp + row * D : nullptr;
+    // (split rows and pooled rows: whole batches only, where row0 = b nb)
+    uint16_t* sp = a.qs ? a.qs + ((int64_t)blockIdx.z * a.heads_q + h) * split_rows(nb) * 3 * DG : nullptr;
+    pool_proj_head<T, D, DG, false, BLK, RS>(q + h * a.q.sh, a.q.ss, chunk, nb, seq_len, a.wq + h * a.wq_head_stride, out,
+                                             smem, srot, a.rope_base, po, sp);
   } else {
     const int g = slot - a.heads_q;
-    const T* x = static_cast<const T*>(a.k.ptr) + b * a.k.sb + g * a.k.sh;
-    float* out = a.kg ? a.kg + ((int64_t)b * a.heads_kv + g) * a.n_blocks * DG : nullptr;
-    float* po = a.kp ? a.kp + ((int64_t)b * a.heads_kv + g) * a.n_blocks * 3 * D : nullptr;
-    uint16_t* sp = a.ks ? a.ks + ((int64_t)b * a.heads_kv + g) * split_rows(a.n_blocks) * 3 * DG : nullptr;
-    pool_proj_head<T, D, DG, true, BLK, RS>(x, a.k.ss, a.n_blocks, a.seq_len, a.wk + g * a.wk_head_stride, out, smem, srot,
-                                   a.rope_base, po, sp);
+    const int64_t row = row0 * a.heads_kv + (int64_t)g * nb;
+    float* out = a.kg ? a.kg + row * DG : nullptr;
+    float* po = a.kp ? a.kp + row * 3 * D : nullptr;
+    uint16_t* sp = a.ks ? a.ks + ((int64_t)blockIdx.z * a.heads_kv + g) * split_rows(nb) * 3 * DG : nullptr;
+    pool_proj_head<T, D, DG, true, BLK, RS>(k + g * a.k.sh, a.k.ss, chunk, nb, seq_len, a.wk + g * a.wk_head_stride, out,
+                                            smem, srot, a.rope_base, po, sp);
   }
+}
+
+template <typename T, int D, int DG, int BLK, int RS>
+__global__ __launch_bounds__(256) void pool_proj_kernel(PoolProjArgs a) {
+  const int b = blockIdx.z;
+  pool_proj_chunk<T, D, DG, BLK, RS>(a, static_cast<const T*>(a.q.ptr) + b * a.q.sb, static_cast<const T*>(a.k.ptr) + b * a.k.sb,
+                                     (int64_t)b * a.n_blocks, blockIdx.x, a.n_blocks, a.seq_len);
+}
+
+// The chunks of several packed sequences in one launch.
+template <typename T, int D, int DG, int BLK, int RS>
+__global__ __launch_bounds__(256) void pool_proj_packed_kernel(PoolProjArgs a, PackedSeqs p) {
+  const int s = packed_find(p.first, p.n, blockIdx.x);
+  const int len = p.len[s];
+  const int64_t t0 = p.tok0[s];
+  pool_proj_chunk<T, D, DG, BLK, RS>(a, static_cast<const T*>(a.q.ptr) + t0 * a.q.ss, static_cast<const T*>(a.k.ptr) + t0 * a.k.ss,
+                                     p.row0[s], (int)blockIdx.x - p.first[s], (len + BLK - 1) / BLK, len);
 }
 
 // Row ranges per block: 4 when the grid of whole-block threads would hold fewer
@@ -283,35 +304,75 @@ static hipError_t pool_proj_launch_rs(const PoolProjArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <typename T, int D, int DG, int RS>
+static hipError_t pool_proj_launch_packed(const PoolProjArgs& a, PackedSeqs p, hipStream_t s) {
+  constexpr int R = PoolTiling<T, D, DG, RS>::R;
+  int chunks = 0;
+  for (int i = 0; i < p.n; ++i) {
+    p.first[i] = chunks;
+    chunks += ((p.len[i] + a.block - 1) / a.block + R - 1) / R;
+  }
+  const dim3 grid(chunks, a.heads_q + a.heads_kv);
+  if (a.block == 64) hipLaunchKernelGGL((pool_proj_packed_kernel<T, D, DG, 64, RS>), grid, dim3(256), 0, s, a, p);
+  else if (a.block == 128) hipLaunchKernelGGL((pool_proj_packed_kernel<T, D, DG, 128, RS>), grid, dim3(256), 0, s, a, p);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 template <typename T, int D, int DG>
-static hipError_t pool_proj_launch(const PoolProjArgs& a, hipStream_t s) {
+static int row_ranges(const PoolProjArgs& a) {
   constexpr int R1 = PoolTiling<T, D, DG, 1>::R;
   const int64_t wgs = (int64_t)((a.n_blocks + R1 - 1) / R1) * (a.heads_q + a.heads_kv) * a.batch;
-  if constexpr (PoolTiling<T, D, DG, 4>::ok) {
-    if (wgs < kPoolSplitWgs) return pool_proj_launch_rs<T, D, DG, 4>(a, s);
+  return PoolTiling<T, D, DG, 4>::ok && wgs < kPoolSplitWgs ? 4 : 1;
+}
+
+// op 0: the ranges of the shape into *ranges; 1: the launch; 2: the packed launch with *ranges.
+template <typename T, int D, int DG>
+static hipError_t pool_proj_op(int op, const PoolProjArgs& a, const PackedSeqs* p, int* ranges, hipStream_t s) {
+  const int rs = op == 2 ? *ranges : row_ranges<T, D, DG>(a);
+  if (op == 0) {
+    *ranges = rs;
+    return hipSuccess;
   }
-  return pool_proj_launch_rs<T, D, DG, 1>(a, s);
+  if constexpr (PoolTiling<T, D, DG, 4>::ok) {
+    if (rs == 4) return op == 2 ? pool_proj_launch_packed<T, D, DG, 4>(a, *p, s) : pool_proj_launch_rs<T, D, DG, 4>(a, s);
+  } else if (op == 2) {
+    return pool_proj_launch_packed<T, D, DG, 1>(a, *p, s);
+  }
+  return op == 2 ? hipErrorInvalidValue : pool_proj_launch_rs<T, D, DG, 1>(a, s);
 }
 
 template <typename T, int D>
-static hipError_t pool_proj_dg(const PoolProjArgs& a, hipStream_t s) {
+static hipError_t pool_proj_dg(int op, const PoolProjArgs& a, const PackedSeqs* p, int* ranges, hipStream_t s) {
   switch (a.gate_dim) {
-    case 32: return pool_proj_launch<T, D, 32>(a, s);
-    case 64: return pool_proj_launch<T, D, 64>(a, s);
-    case 128: return pool_proj_launch<T, D, 128>(a, s);
+    case 32: return pool_proj_op<T, D, 32>(op, a, p, ranges, s);
+    case 64: return pool_proj_op<T, D, 64>(op, a, p, ranges, s);
+    case 128: return pool_proj_op<T, D, 128>(op, a, p, ranges, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_pool_proj(const PoolProjArgs& a, hipStream_t s) {
+static hipError_t pool_proj_any(int op, const PoolProjArgs& a, const PackedSeqs* p, int* ranges, hipStream_t s) {
   if (a.bf16) {
-    if (a.head_dim == 64) return pool_proj_dg<uint16_t, 64>(a, s);
-    if (a.head_dim == 128) return pool_proj_dg<uint16_t, 128>(a, s);
+    if (a.head_dim == 64) return pool_proj_dg<uint16_t, 64>(op, a, p, ranges, s);
+    if (a.head_dim == 128) return pool_proj_dg<uint16_t, 128>(op, a, p, ranges, s);
   } else {
-    if (a.head_dim == 64) return pool_proj_dg<float, 64>(a, s);
-    if (a.head_dim == 128) return pool_proj_dg<float, 128>(a, s);
+    if (a.head_dim == 64) return pool_proj_dg<float, 64>(op, a, p, ranges, s);
+    if (a.head_dim == 128) return pool_proj_dg<float, 128>(op, a, p, ranges, s);
   }
   return hipErrorInvalidValue;
+}
+
+int pool_row_ranges(const PoolProjArgs& a) {
+  int r = 0;
+  return pool_proj_any(0, a, nullptr, &r, nullptr) == hipSuccess ? r : 0;
+}
+
+hipError_t launch_pool_proj(const PoolProjArgs& a, hipStream_t s) { return pool_proj_any(1, a, nullptr, nullptr, s); }
+
+hipError_t launch_pool_proj_packed(const PoolProjArgs& a, const PackedSeqs& seqs, int ranges, hipStream_t s) {
+  if (seqs.n < 1 || seqs.n > kPackMax || a.qp || a.kp || a.qs || a.ks) return hipErrorInvalidValue;
+  return pool_proj_any(2, a, &seqs, &ranges, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -844,20 +905,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void s
 constexpr int kFusedRows = 16;
 constexpr int kFusedMaxBlocks = 2048;
 
+// Rows i0 = 16 chunk .. i0 + 15 of query head h of one sequence: q its head's
+// projected rows, k its KV head's; row0: the mask row of query block 0.
 template <int MAXM, int DG>
-__global__ __launch_bounds__(1024) void gate_fused_kernel(GateFusedArgs a) {
+__device__ __forceinline__ void gate_fused_chunk(const GateFusedArgs& a, const SelectArgs& sel, const float* q, const float* k,
+                                                 int chunk, int h, int64_t row0) {
   constexpr int LDL = 64 * MAXM + 4;
   constexpr int WORDS = kFusedRows * LDL > kFusedRows * 256 ? kFusedRows * LDL : kFusedRows * 256;
   __shared__ __attribute__((aligned(16))) float sL[WORDS];
-  const int nb = a.sel.n_blocks;
-  const int chunks = (nb + kFusedRows - 1) / kFusedRows;
-  // 1-D grid, heaviest rows first over the whole launch (head by head, the
-  // last heads' heavy rows would run alone at the end: measured 0.93 -> 0.86 ms
-  // at 131072 tokens, 0.178 -> 0.153 ms at 32768)
-  const int nbh = a.sel.batch * a.sel.heads_q;
-  const int chunk = chunks - 1 - (int)blockIdx.x / nbh;
-  const int h = (int)blockIdx.x % nbh % a.sel.heads_q, b = (int)blockIdx.x % nbh / a.sel.heads_q;
-  const int g = h / (a.sel.heads_q / a.heads_kv);
+  const int nb = sel.n_blocks;
   const int i0 = kFusedRows * chunk;
   const int ncols = min(nb, i0 + kFusedRows);  // block-causal: columns j <= i0 + 15
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
@@ -867,7 +923,7 @@ __global__ __launch_bounds__(1024) void gate_fused_kernel(GateFusedArgs a) {
   // phase 1: logits of rows i0 .. i0 + 15 (rows past nb repeat the last one)
   float qa[KS];
   {
-    const float* qrow = a.qg + (((int64_t)b * a.sel.heads_q + h) * nb + min(i0 + r16, nb - 1)) * DG + kq * KS;
+    const float* qrow = q + (int64_t)min(i0 + r16, nb - 1) * DG + kq * KS;
 #pragma unroll
     for (int u = 0; u < KS / 4; ++u) {
       const f32x4 x = *reinterpret_cast<const f32x4*>(qrow + 4 * u);
@@ -875,7 +931,7 @@ __global__ __launch_bounds__(1024) void gate_fused_kernel(GateFusedArgs a) {
       for (int e = 0; e < 4; ++e) qa[4 * u + e] = x[e];
     }
   }
-  const float* kbase = a.kg + ((int64_t)b * a.heads_kv + g) * nb * DG + kq * KS;
+  const float* kbase = k + kq * KS;
   // the next column tile's operands load while the current one multiplies
   auto load_k = [&](int ct, f32x4 (&kb)[KS / 4]) {
     const float* krow = kbase + (int64_t)min(16 * ct + r16, nb - 1) * DG;
@@ -910,9 +966,43 @@ __global__ __launch_bounds__(1024) void gate_fused_kernel(GateFusedArgs a) {
   }
   __syncthreads();  // every row is in registers: the LDS now holds the histograms
   if (i >= nb) return;
-  const int64_t row = ((int64_t)b * a.sel.heads_q + h) * nb + i;
-  select_emit<MAXM>(a.sel, v, i, h, row, reinterpret_cast<uint32_t*>(sL) + 256 * wave);
+  select_emit<MAXM>(sel, v, i, h, row0 + i, reinterpret_cast<uint32_t*>(sL) + 256 * wave);
 }
+
+template <int MAXM, int DG>
+__global__ __launch_bounds__(1024) void gate_fused_kernel(GateFusedArgs a) {
+  const int nb = a.sel.n_blocks;
+  const int chunks = (nb + kFusedRows - 1) / kFusedRows;
+  // 1-D grid, heaviest rows first over the whole launch (head by head, the
+  // last heads' heavy rows would run alone at the end: measured 0.93 -> 0.86 ms
+  // at 131072 tokens, 0.178 -> 0.153 ms at 32768)
+  const int nbh = a.sel.batch * a.sel.heads_q;
+  const int chunk = chunks - 1 - (int)blockIdx.x / nbh;
+  const int h = (int)blockIdx.x % nbh % a.sel.heads_q, b = (int)blockIdx.x % nbh / a.sel.heads_q;
+  const int g = h / (a.sel.heads_q / a.heads_kv);
+  const int64_t row0 = ((int64_t)b * a.sel.heads_q + h) * nb;
+  gate_fused_chunk<MAXM, DG>(a, a.sel, a.qg + row0 * DG, a.kg + ((int64_t)b * a.heads_kv + g) * nb * DG, chunk, h, row0);
+}
+
+// The chunks of several packed sequences in one launch (rows of at most 128
+// blocks: MAXM 2 serves them all).
+template <int DG>
+__global__ __launch_bounds__(1024) void gate_fused_packed_kernel(GateFusedArgs a, PackedSeqs p, int block) {
+  const int s = packed_find(p.first, p.n, blockIdx.x);
+  const int hq = a.sel.heads_q;
+  SelectArgs sel = a.sel;
+  const int nb = sel.n_blocks = (p.len[s] + block - 1) / block;
+  const int r = (int)blockIdx.x - p.first[s];
+  const int chunk = (nb + kFusedRows - 1) / kFusedRows - 1 - r / hq;
+  const int h = r % hq, g = h / (hq / a.heads_kv);
+  sel.count += (int64_t)p.mrow[s] * hq;
+  sel.idx += p.midx[s] * hq;
+  if (sel.dense) sel.dense += p.midx[s] * hq;
+  const int64_t r0 = p.row0[s];
+  gate_fused_chunk<2, DG>(a, sel, a.qg + (r0 * hq + (int64_t)h * nb) * DG, a.kg + (r0 * a.heads_kv + (int64_t)g * nb) * DG,
+                          chunk, h, (int64_t)h * nb);
+}
+
 
 // Static scratch of seer_gate_noalloc: the projected rows Qg and Kg (the fused
 // kernel needs no logits buffer).  Every call on a device shares that device's
@@ -962,6 +1052,27 @@ hipError_t launch_gate_fused(const GateFusedArgs& a, hipStream_t s) {
   if (m <= 8) return gate_fused_dg<8>(a, s);
   if (m <= 16) return gate_fused_dg<16>(a, s);
   return gate_fused_dg<32>(a, s);
+}
+
+hipError_t launch_gate_fused_packed(const GateFusedArgs& a, const PackedSeqs& seqs, int block, hipStream_t s) {
+  if (seqs.n < 1 || seqs.n > kPackMax || a.sel.group > 0) return hipErrorInvalidValue;
+  PackedSeqs p = seqs;
+  int64_t wgs = 0;
+  for (int i = 0; i < p.n; ++i) {
+    const int nb = (p.len[i] + block - 1) / block;
+    if (nb < 1 || nb > kFusedPackedBlocks) return hipErrorInvalidValue;
+    p.first[i] = (int)wgs;
+    wgs += (int64_t)(nb + kFusedRows - 1) / kFusedRows * a.sel.heads_q;
+  }
+  if (wgs > INT32_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)wgs);
+  switch (a.gate_dim) {
+    case 32: hipLaunchKernelGGL(gate_fused_packed_kernel<32>, grid, dim3(1024), 0, s, a, p, block); break;
+    case 64: hipLaunchKernelGGL(gate_fused_packed_kernel<64>, grid, dim3(1024), 0, s, a, p, block); break;
+    case 128: hipLaunchKernelGGL(gate_fused_packed_kernel<128>, grid, dim3(1024), 0, s, a, p, block); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 template <int MAXM>

@@ -15,6 +15,17 @@ struct TensorView {  // [batch][heads][seq][dim], element strides of (batch, hea
 // Rows of one head's split gate rows: nb rounded up to whole 32-row groups.
 __host__ __device__ __forceinline__ int split_rows(int nb) { return (nb + 31) / 32 * 32; }
 
+// Sequences of a packed variable-length batch that one launch serves together.
+// first[s]: the sequence's first workgroup (filled by each launcher; ascending);
+// tok0, len: its tokens; mrow, midx: count rows and idx entries of the packed
+// mask before it, per mask head; row0: gate scratch rows before it, per head.
+constexpr int kPackMax = 64;  // one per lane of a wavefront (packed_find)
+struct PackedSeqs {
+  int n;
+  int first[kPackMax], tok0[kPackMax], len[kPackMax], mrow[kPackMax], row0[kPackMax];
+  int64_t midx[kPackMax];
+};
+
 struct PoolProjArgs {
   TensorView q, k;
   int batch, heads_q, heads_kv, n_blocks, head_dim, gate_dim;
@@ -172,16 +183,30 @@ struct RopeArgs {  // inverse block-level RoPE of rows [rows][nb][Dg], in place
 };
 
 hipError_t launch_pool_proj(const PoolProjArgs& a, hipStream_t s);
+// Row ranges per block that launch_pool_proj takes for this shape (the order in
+// which a block's rows are summed), and the packed form of the launch: every
+// sequence must take `ranges` when launched alone.
+int pool_row_ranges(const PoolProjArgs& a);
+hipError_t launch_pool_proj_packed(const PoolProjArgs& a, const PackedSeqs& seqs, int ranges, hipStream_t s);
 hipError_t launch_kl_rows(const KlArgs& a, hipStream_t s);
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
 hipError_t launch_rope_inverse(const RopeArgs& a, hipStream_t s);
 hipError_t launch_gate_logits(const GateLogitsArgs& a, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_gate_fused(const GateFusedArgs& a, hipStream_t s);
+// The packed form, for sequences of at most kFusedPackedBlocks blocks.
+constexpr int kFusedPackedBlocks = 128;
+hipError_t launch_gate_fused_packed(const GateFusedArgs& a, const PackedSeqs& seqs, int block, hipStream_t s);
 hipError_t launch_mask_from_dense(const MaskFromDenseArgs& a, hipStream_t s);
 // With a non-null `count` nothing is launched: the attention-kernel launches
 // the call would make are counted into *count.
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s, int* count = nullptr);
+// Sparse attention of the sequences of a packed batch in one launch (bf16, no
+// options): `a` describes the packed tensors and the packed mask, its seq_len,
+// n_blocks and mask_blocks are the sequences' own.
+hipError_t launch_attn_packed(const AttnArgs& a, const PackedSeqs& seqs, hipStream_t s);
+// Whether a sequence of n_blocks tiles joins such a launch.
+bool attn_packs(const AttnArgs& a, int n_blocks);
 // Split geometry: the key-range width in blocks for a launch (0 when the shape
 // does not split) and the partial slots per (batch, head) for a range width.
 int split_width(int n_blocks, int head_dim, bool causal, bool bf16, bool want, int width);

@@ -8,6 +8,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <memory>
+#include <new>
 
 #include "launch.h"
 #include "seer.h"
@@ -368,7 +370,71 @@ size_t seer_mask_idx_elems(const seer_attn_desc* desc, int32_t block) {
 }
 
 // Longest gate rows (in blocks) that seer_gate selects with the fused kernel.
-constexpr int kFusedGateMaxBlocks = 128;
+constexpr int kFusedGateMaxBlocks = seer::kFusedPackedBlocks;
+
+// The gate's kernel arguments without their scratch rows (null).
+static seer::PoolProjArgs pool_args(const seer_attn_desc* desc, const seer_gate_desc* gate, const void* q, const void* k,
+                                    const float* wq, const float* wk) {
+  const int D = desc->head_dim, Dg = gate->gate_dim;
+  seer::PoolProjArgs pa;
+  pa.q = view(q, desc->q_stride);
+  pa.k = view(k, desc->k_stride);
+  pa.batch = desc->batch;
+  pa.heads_q = desc->heads_q;
+  pa.heads_kv = desc->heads_kv;
+  pa.n_blocks = blocks_of(desc->seq_len, gate->block);
+  pa.head_dim = D;
+  pa.gate_dim = Dg;
+  pa.bf16 = desc->dtype == SEER_BF16;
+  pa.wq = wq;
+  pa.wk = wk;
+  pa.wq_head_stride = gate->w_per_head ? (int64_t)D * Dg : 0;
+  pa.wk_head_stride = gate->w_per_head ? (int64_t)3 * D * Dg : 0;
+  pa.qg = nullptr;
+  pa.kg = nullptr;
+  pa.rope_base = gate->rope_theta > 0.0 ? gate->rope_theta / gate->block : 0.0;
+  pa.qp = nullptr;
+  pa.kp = nullptr;
+  pa.qs = nullptr;
+  pa.ks = nullptr;
+  pa.block = gate->block;
+  pa.seq_len = desc->seq_len;
+  return pa;
+}
+
+// The selection's arguments without its logits and row length.
+static seer::SelectArgs select_args(const seer_attn_desc* desc, const seer_gate_desc* gate, const seer_block_mask* out) {
+  seer::SelectArgs sa;
+  sa.logits = nullptr;
+  sa.batch = desc->batch;
+  sa.heads_q = desc->heads_q;
+  sa.n_blocks = 0;
+  sa.mode = gate->mode;
+  sa.topk_ratio = gate->topk_ratio;
+  sa.topk_k = gate->topk_k;
+  sa.threshold = gate->threshold;
+  sa.head_thresholds = gate->mode == SEER_THRESHOLD ? gate->head_thresholds : nullptr;
+  sa.keep_first = gate->keep_first ? 1 : 0;
+  sa.keep_diag = gate->keep_diag ? 1 : 0;
+  sa.group = gate->kv_shared ? desc->heads_q / desc->heads_kv : 0;
+  sa.count = out->count;
+  sa.idx = out->idx;
+  sa.dense = out->dense;
+  return sa;
+}
+
+// Whether the gate's fused score + select kernel serves this call.
+//
+// Short rows take it, and its logits never leave LDS (16 rows per workgroup; at
+// up to 128 blocks several workgroups share a CU).  Longer rows fill 64-128 KiB
+// of LDS per workgroup, which leaves one workgroup per CU and no overlap of its
+// MFMA and selection phases: measured gate 0.059 against 0.067 ms at 8192 tokens
+// (32 query / 8 KV heads), but 0.173 against 0.143 ms at 32768 and 0.92 against
+// 0.76 ms at 131072.
+static bool gate_fuses(const seer_gate_desc* gate, int nb, const float* logits_out) {
+  return logits_out == nullptr && !gate->kv_shared && nb <= kFusedGateMaxBlocks &&
+         seer::gate_fused_supported(nb, gate->gate_dim);
+}
 
 // The gate after argument checks.  fused: the logits are formed and selected
 // in one kernel (gate_fused_kernel) and never leave on-chip memory, so the
@@ -387,32 +453,14 @@ static seer_status gate_run(const seer_attn_desc* desc, const seer_gate_desc* ga
   uint16_t* qs = fused ? nullptr : reinterpret_cast<uint16_t*>(ws + L.qs);
   uint16_t* ks = fused ? nullptr : reinterpret_cast<uint16_t*>(ws + L.ks);
   float* logits = logits_in_ws ? reinterpret_cast<float*>(ws + L.logits) : logits_out;
-  const int D = desc->head_dim, Dg = gate->gate_dim;
+  const int Dg = gate->gate_dim;
 
-  seer::PoolProjArgs pa;
-  pa.q = view(q, desc->q_stride);
-  pa.k = view(k, desc->k_stride);
-  pa.batch = desc->batch;
-  pa.heads_q = desc->heads_q;
-  pa.heads_kv = desc->heads_kv;
-  pa.n_blocks = nb;
-  pa.head_dim = D;
-  pa.gate_dim = Dg;
-  pa.bf16 = desc->dtype == SEER_BF16;
-  pa.wq = wq;
-  pa.wk = wk;
-  pa.wq_head_stride = gate->w_per_head ? (int64_t)D * Dg : 0;
-  pa.wk_head_stride = gate->w_per_head ? (int64_t)3 * D * Dg : 0;
+  seer::PoolProjArgs pa = pool_args(desc, gate, q, k, wq, wk);
   // the fused kernel reads the fp32 rows, the logits kernel only their parts
   pa.qg = fused ? qg : nullptr;
   pa.kg = fused ? kg : nullptr;
-  pa.rope_base = gate->rope_theta > 0.0 ? gate->rope_theta / gate->block : 0.0;
-  pa.qp = nullptr;
-  pa.kp = nullptr;
   pa.qs = qs;
   pa.ks = ks;
-  pa.block = gate->block;
-  pa.seq_len = desc->seq_len;
   if ((s = from_hip(seer::launch_pool_proj(pa, st))) != SEER_OK) return s;
 
   const float scale = (float)(1.0 / std::sqrt((double)Dg));
@@ -430,22 +478,9 @@ static seer_status gate_run(const seer_attn_desc* desc, const seer_gate_desc* ga
     if ((s = from_hip(seer::launch_gate_logits(la, st))) != SEER_OK) return s;
   }
 
-  seer::SelectArgs sa;
+  seer::SelectArgs sa = select_args(desc, gate, out);
   sa.logits = fused ? nullptr : logits;
-  sa.batch = desc->batch;
-  sa.heads_q = desc->heads_q;
   sa.n_blocks = nb;
-  sa.mode = gate->mode;
-  sa.topk_ratio = gate->topk_ratio;
-  sa.topk_k = gate->topk_k;
-  sa.threshold = gate->threshold;
-  sa.head_thresholds = gate->mode == SEER_THRESHOLD ? gate->head_thresholds : nullptr;
-  sa.keep_first = gate->keep_first ? 1 : 0;
-  sa.keep_diag = gate->keep_diag ? 1 : 0;
-  sa.group = gate->kv_shared ? desc->heads_q / desc->heads_kv : 0;
-  sa.count = out->count;
-  sa.idx = out->idx;
-  sa.dense = out->dense;
   if (fused) {
     seer::GateFusedArgs fa;
     fa.qg = qg;
@@ -471,14 +506,7 @@ seer_status seer_gate(const seer_attn_desc* desc, const seer_gate_desc* gate, co
   const GateLayout L = gate_layout(desc, gate, logits_out == nullptr);
   if (!workspace || workspace_bytes < L.total) return SEER_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign != 0) return SEER_ERR_INVALID_ARG;
-  // Short rows take the fused score + select kernel, whose logits never leave
-  // LDS (16 rows per workgroup; at up to 128 blocks several workgroups share a
-  // CU).  Longer rows fill 64-128 KiB of LDS per workgroup, which leaves one
-  // workgroup per CU and no overlap of its MFMA and selection phases: measured
-  // gate 0.059 against 0.067 ms at 8192 tokens (32 query / 8 KV heads), but
-  // 0.173 against 0.143 ms at 32768 and 0.92 against 0.76 ms at 131072.
-  const bool fused = logits_out == nullptr && !gate->kv_shared && nb <= kFusedGateMaxBlocks &&
-                     seer::gate_fused_supported(nb, gate->gate_dim);
+  const bool fused = gate_fuses(gate, nb, logits_out);
   return gate_run(desc, gate, q, k, wq, wk, out, logits_out, workspace, fused, static_cast<hipStream_t>(stream));
 }
 
@@ -723,29 +751,13 @@ seer_status seer_gate_distill(const seer_attn_desc* desc, const seer_gate_desc* 
   const float rsqrt_dg = (float)(1.0 / std::sqrt((double)Dg));
 
   // forward: pooled rows (kept), projected rows, logits
-  seer::PoolProjArgs pa;
-  pa.q = view(q, desc->q_stride);
-  pa.k = view(k, desc->k_stride);
-  pa.batch = B;
-  pa.heads_q = Hq;
-  pa.heads_kv = Hkv;
-  pa.n_blocks = nb;
-  pa.head_dim = D;
-  pa.gate_dim = Dg;
-  pa.bf16 = desc->dtype == SEER_BF16;
-  pa.wq = wq;
-  pa.wk = wk;
-  pa.wq_head_stride = gate->w_per_head ? (int64_t)D * Dg : 0;
-  pa.wk_head_stride = gate->w_per_head ? (int64_t)3 * D * Dg : 0;
+  seer::PoolProjArgs pa = pool_args(desc, gate, q, k, wq, wk);
   pa.qg = qg;
   pa.kg = kg;
-  pa.rope_base = rope_base;
   pa.qp = qp;
   pa.kp = kp;
   pa.qs = qs;
   pa.ks = ks;
-  pa.block = gate->block;
-  pa.seq_len = desc->seq_len;
   if ((s = from_hip(seer::launch_pool_proj(pa, st))) != SEER_OK) return s;
 
   seer::GateLogitsArgs la;
@@ -788,7 +800,8 @@ seer_status seer_gate_distill(const seer_attn_desc* desc, const seer_gate_desc* 
 }  // extern "C"
 
 // ---------------------------------------------------------------------------
-// packed variable-length batches: one batch-1 pass per sequence on the stream
+// packed variable-length batches: short sequences share launches, the others
+// run one batch-1 pass each on the stream
 // ---------------------------------------------------------------------------
 
 namespace {
@@ -832,6 +845,115 @@ VarlenMaskOffsets varlen_mask_offsets(const int32_t* cu, int b, int heads, int b
   return o;
 }
 
+// Scratch rows of the sequences that share one gate launch: bounded, as one
+// launch of this many already fills the GPU (26 sequences of 8192 tokens at 32
+// query / 8 KV heads of 128).
+constexpr size_t kPackedGateBytes = (size_t)64 << 20;
+
+size_t gate_row_bytes(const seer_gate_desc* g, int heads, int64_t rows) {
+  return round_up((size_t)heads * rows * g->gate_dim * 4);
+}
+
+size_t packed_gate_bytes(const seer_attn_desc* d, const seer_gate_desc* g, int64_t rows) {
+  return gate_row_bytes(g, d->heads_q, rows) + gate_row_bytes(g, d->heads_kv, rows);
+}
+
+// The row ranges a sequence pools with, 0 when it does not share gate launches.
+int packed_gate_class(const seer_attn_desc* sd, const seer_gate_desc* gate) {
+  if (!gate_fuses(gate, blocks_of(sd->seq_len, gate->block), nullptr)) return 0;
+  return seer::pool_row_ranges(pool_args(sd, gate, nullptr, nullptr, nullptr, nullptr));
+}
+
+// One sequence of a packed batch: its tokens, and the mask rows and entries per
+// mask head of the sequences before it.
+struct SeqRef {
+  int b, tok0, len;
+  int64_t mrow, midx;
+};
+
+// The non-empty sequences, longest first (equal lengths in order).  Null when
+// the host has no memory for the list (the callers then run the sequences one
+// by one).
+struct SeqList {
+  std::unique_ptr<SeqRef[]> refs;
+  int n = 0;
+  SeqList(const int32_t* cu, int batch, int block) : refs(new (std::nothrow) SeqRef[batch]) {
+    if (!refs) return;
+    int64_t mrow = 0, midx = 0;
+    for (int b = 0; b < batch; ++b) {
+      const int len = cu[b + 1] - cu[b];
+      if (len == 0) continue;
+      refs[n++] = SeqRef{b, cu[b], len, mrow, midx};
+      const int64_t nb = blocks_of(len, block);
+      mrow += nb;
+      midx += nb * nb;
+    }
+    std::sort(refs.get(), refs.get() + n, [](const SeqRef& x, const SeqRef& y) {
+      return x.len != y.len ? x.len > y.len : x.b < y.b;
+    });
+  }
+};
+
+// Sequences gathered for a shared launch: at most kPackMax, with workgroup
+// counts that stay far from the range of int.
+struct Packer {
+  seer::PackedSeqs p{};
+  int64_t rows = 0;  // gate scratch rows per head
+  int64_t work = 0;  // (head, block) pairs
+  bool fits(int64_t more) const { return p.n < seer::kPackMax && work + more <= INT32_MAX / 2; }
+  void add(const SeqRef& r, int nb, int64_t more) {
+    p.tok0[p.n] = r.tok0;
+    p.len[p.n] = r.len;
+    p.mrow[p.n] = (int)r.mrow;
+    p.midx[p.n] = r.midx;
+    p.row0[p.n] = (int)rows;
+    rows += nb;
+    work += more;
+    ++p.n;
+  }
+  void clear() {
+    p.n = 0;
+    rows = work = 0;
+  }
+};
+
+// The gate of one sequence of a packed batch, by itself.
+seer_status gate_sequence(const seer_attn_desc* desc, const int32_t* cu, const seer_gate_desc* gate, const void* q,
+                          const void* k, const float* wq, const float* wk, const seer_block_mask* out, int b, int64_t mrow,
+                          int64_t midx, void* workspace, size_t workspace_bytes, void* stream) {
+  const size_t es = elem_size(desc->dtype);
+  const int64_t heads = gate->kv_shared ? desc->heads_kv : desc->heads_q;
+  const seer_attn_desc sd = seq_desc(desc, cu, b);
+  seer_block_mask m = *out;
+  m.n_blocks = blocks_of(sd.seq_len, gate->block);
+  m.count = out->count + heads * mrow;
+  m.idx = out->idx + heads * midx;
+  m.dense = out->dense ? out->dense + heads * midx : nullptr;
+  return seer_gate(&sd, gate, at_token(q, desc->q_stride, cu[b], es), at_token(k, desc->k_stride, cu[b], es), wq, wk, &m,
+                   nullptr, workspace, workspace_bytes, stream);
+}
+
+// The gate of the gathered sequences: one pooling and one score + select launch.
+seer_status gate_packed(const seer_attn_desc* desc, const seer_gate_desc* gate, const void* q, const void* k, const float* wq,
+                        const float* wk, const seer_block_mask* out, const Packer& pk, int ranges, void* workspace,
+                        hipStream_t st) {
+  seer_attn_desc one = *desc;
+  one.batch = 1;
+  seer::PoolProjArgs pa = pool_args(&one, gate, q, k, wq, wk);
+  pa.qg = static_cast<float*>(workspace);
+  pa.kg = reinterpret_cast<float*>(static_cast<char*>(workspace) + gate_row_bytes(gate, desc->heads_q, pk.rows));
+  const seer_status s = from_hip(seer::launch_pool_proj_packed(pa, pk.p, ranges, st));
+  if (s != SEER_OK) return s;
+  seer::GateFusedArgs fa;
+  fa.qg = pa.qg;
+  fa.kg = pa.kg;
+  fa.heads_kv = desc->heads_kv;
+  fa.gate_dim = gate->gate_dim;
+  fa.scale = (float)(1.0 / std::sqrt((double)gate->gate_dim));
+  fa.sel = select_args(&one, gate, out);
+  return from_hip(seer::launch_gate_fused_packed(fa, pk.p, gate->block, st));
+}
+
 }  // namespace
 
 extern "C" {
@@ -851,13 +973,15 @@ size_t seer_gate_varlen_workspace_bytes(const seer_attn_desc* desc, const int32_
                                         const seer_gate_desc* gate) {
   if (check_cu(desc, cu_seqlens_host) != SEER_OK) return 0;
   size_t need = 0;
+  int64_t rows = 0;  // of the sequences that share launches
   for (int b = 0; b < desc->batch; ++b) {
     const seer_attn_desc sd = seq_desc(desc, cu_seqlens_host, b);
     if (sd.seq_len == 0) continue;
     if (check_gate(&sd, gate) != SEER_OK) return 0;
     need = std::max(need, gate_layout(&sd, gate, true).total);
+    if (packed_gate_class(&sd, gate) != 0) rows += blocks_of(sd.seq_len, gate->block);
   }
-  return need;
+  return std::max(need, std::min(packed_gate_bytes(desc, gate, rows), kPackedGateBytes));
 }
 
 seer_status seer_gate_varlen(const seer_attn_desc* desc, const int32_t* cu_seqlens_host,
@@ -869,7 +993,6 @@ seer_status seer_gate_varlen(const seer_attn_desc* desc, const int32_t* cu_seqle
   if (!gate || !out || !out->count || !out->idx || !q || !k) return SEER_ERR_INVALID_ARG;
   if (out->kv_shared != gate->kv_shared) return SEER_ERR_INVALID_ARG;
   const size_t es = elem_size(desc->dtype);
-  const int heads = gate->kv_shared ? desc->heads_kv : desc->heads_q;
   // validate every sequence before launching anything
   for (int b = 0; b < desc->batch; ++b) {
     const seer_attn_desc sd = seq_desc(desc, cu_seqlens_host, b);
@@ -880,19 +1003,51 @@ seer_status seer_gate_varlen(const seer_attn_desc* desc, const int32_t* cu_seqle
         !aligned16(at_token(k, desc->k_stride, cu_seqlens_host[b], es)))
       return SEER_ERR_INVALID_ARG;
   }
-  for (int b = 0; b < desc->batch; ++b) {
-    const seer_attn_desc sd = seq_desc(desc, cu_seqlens_host, b);
-    if (sd.seq_len == 0) continue;
-    const VarlenMaskOffsets o = varlen_mask_offsets(cu_seqlens_host, b, heads, gate->block);
-    seer_block_mask m = *out;
-    m.n_blocks = blocks_of(sd.seq_len, gate->block);
-    m.count = out->count + o.count;
-    m.idx = out->idx + o.idx;
-    m.dense = out->dense ? out->dense + o.idx : nullptr;
-    s = seer_gate(&sd, gate, at_token(q, desc->q_stride, cu_seqlens_host[b], es),
-                  at_token(k, desc->k_stride, cu_seqlens_host[b], es), wq, wk, &m, nullptr, workspace,
-                  workspace_bytes, stream);
-    if (s != SEER_OK) return s;
+  if (desc->seq_len == 0) return SEER_OK;
+  if (!wq || !wk || !aligned16(wq) || !aligned16(wk) || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0)
+    return SEER_ERR_INVALID_ARG;
+  const SeqList list(cu_seqlens_host, desc->batch, gate->block);
+  if (!list.refs) {
+    for (int b = 0; b < desc->batch; ++b) {
+      if (cu_seqlens_host[b + 1] == cu_seqlens_host[b]) continue;
+      const VarlenMaskOffsets o = varlen_mask_offsets(cu_seqlens_host, b, 1, gate->block);
+      if ((s = gate_sequence(desc, cu_seqlens_host, gate, q, k, wq, wk, out, b, o.count, o.idx, workspace, workspace_bytes,
+                             stream)) != SEER_OK)
+        return s;
+    }
+    return SEER_OK;
+  }
+  // The sequences that the fused kernel serves share two launches (as many of
+  // them as the workspace holds at once), those of one pooling row split (the
+  // order in which a block's rows are summed) together, so that every mask is
+  // the one of a separate call; the others run alone.  Measured: 20 prompts of
+  // 15 to 6100 tokens (32 query / 8 KV heads of 128) 482 -> 102 us.
+  for (const int cls : {0, 4, 1}) {
+    Packer pk;
+    auto flush = [&]() -> seer_status {
+      if (pk.p.n == 0) return SEER_OK;
+      const seer_status e = gate_packed(desc, gate, q, k, wq, wk, out, pk, cls, workspace, static_cast<hipStream_t>(stream));
+      pk.clear();
+      return e;
+    };
+    for (int x = 0; x < list.n; ++x) {
+      const SeqRef& r = list.refs[x];
+      const seer_attn_desc sd = seq_desc(desc, cu_seqlens_host, r.b);
+      if (packed_gate_class(&sd, gate) != cls) continue;
+      if (cls == 0) {
+        if ((s = gate_sequence(desc, cu_seqlens_host, gate, q, k, wq, wk, out, r.b, r.mrow, r.midx, workspace,
+                               workspace_bytes, stream)) != SEER_OK)
+          return s;
+        continue;
+      }
+      const int nb = blocks_of(r.len, gate->block);
+      const int64_t work = (int64_t)nb * (desc->heads_q + desc->heads_kv);
+      if (!pk.fits(work) || packed_gate_bytes(desc, gate, pk.rows + nb) > workspace_bytes) {
+        if ((s = flush()) != SEER_OK) return s;
+      }
+      pk.add(r, nb, work);
+    }
+    if ((s = flush()) != SEER_OK) return s;
   }
   return SEER_OK;
 }
@@ -906,7 +1061,7 @@ seer_status seer_bsattn_varlen(const seer_attn_desc* desc, const int32_t* cu_seq
   if (block != 64 && block != 128) return SEER_ERR_UNSUPPORTED;
   if (mask->kv_shared != 0 && mask->kv_shared != 1) return SEER_ERR_INVALID_ARG;
   const size_t es = elem_size(desc->dtype);
-  const int heads = mask->kv_shared ? desc->heads_kv : desc->heads_q;
+  const int64_t heads = mask->kv_shared ? desc->heads_kv : desc->heads_q;
   for (int b = 0; b < desc->batch; ++b) {
     const seer_attn_desc sd = seq_desc(desc, cu_seqlens_host, b);
     if (sd.seq_len == 0) continue;
@@ -917,24 +1072,57 @@ seer_status seer_bsattn_varlen(const seer_attn_desc* desc, const int32_t* cu_seq
       return s;
     if (blocks_of(sd.seq_len, block) > 65536) return SEER_ERR_UNSUPPORTED;
   }
-  for (int b = 0; b < desc->batch; ++b) {
+  auto alone = [&](int b, int64_t mrow, int64_t midx) -> seer_status {
     const seer_attn_desc sd = seq_desc(desc, cu_seqlens_host, b);
-    if (sd.seq_len == 0) continue;
-    const VarlenMaskOffsets mo = varlen_mask_offsets(cu_seqlens_host, b, heads, block);
     seer_block_mask m = *mask;
     m.n_blocks = blocks_of(sd.seq_len, block);
-    m.count = mask->count + mo.count;
-    m.idx = mask->idx + mo.idx;
+    m.count = mask->count + heads * mrow;
+    m.idx = mask->idx + heads * midx;
     m.dense = nullptr;
     float* lb = lse ? lse + (int64_t)desc->heads_q * cu_seqlens_host[b] : nullptr;  // [Hq][len_b] per sequence
-    s = attn_common(&sd, block, &m, causal, sm_scale, at_token(q, desc->q_stride, cu_seqlens_host[b], es),
-                    at_token(k, desc->k_stride, cu_seqlens_host[b], es),
-                    at_token(v, desc->v_stride, cu_seqlens_host[b], es),
-                    const_cast<void*>(at_token(o, desc->o_stride, cu_seqlens_host[b], es)), lb, nullptr, 0,
-                    nullptr, stream);
-    if (s != SEER_OK) return s;
+    return attn_common(&sd, block, &m, causal, sm_scale, at_token(q, desc->q_stride, cu_seqlens_host[b], es),
+                       at_token(k, desc->k_stride, cu_seqlens_host[b], es),
+                       at_token(v, desc->v_stride, cu_seqlens_host[b], es),
+                       const_cast<void*>(at_token(o, desc->o_stride, cu_seqlens_host[b], es)), lb, nullptr, 0,
+                       nullptr, stream);
+  };
+  const SeqList list(cu_seqlens_host, desc->batch, block);
+  if (!list.refs) {
+    for (int b = 0; b < desc->batch; ++b) {
+      if (cu_seqlens_host[b + 1] == cu_seqlens_host[b]) continue;
+      const VarlenMaskOffsets o = varlen_mask_offsets(cu_seqlens_host, b, 1, block);
+      if ((s = alone(b, o.count, o.idx)) != SEER_OK) return s;
+    }
+    return SEER_OK;
   }
-  return SEER_OK;
+  // long sequences one by one, then the others together (attn_packs).  Measured:
+  // the 20 prompts above 448 -> 320 us.
+  seer_attn_desc one = *desc;
+  one.batch = 1;
+  seer::AttnArgs a = attn_args(&one, causal, sm_scale, q, k, v, o, lse);
+  a.count = mask->count;
+  a.idx = mask->idx;
+  a.mask_shift = block == 128 ? 1 : 0;
+  a.mask_kv = mask->kv_shared != 0;
+  Packer pk;
+  auto flush = [&]() -> seer_status {
+    if (pk.p.n == 0) return SEER_OK;
+    const seer_status e = from_hip(seer::launch_attn_packed(a, pk.p, static_cast<hipStream_t>(stream)));
+    pk.clear();
+    return e;
+  };
+  for (int x = 0; x < list.n; ++x) {
+    const SeqRef& r = list.refs[x];
+    const int nb = blocks_of(r.len, SEER_BLOCK);
+    if (!seer::attn_packs(a, nb)) {
+      if ((s = alone(r.b, r.mrow, r.midx)) != SEER_OK) return s;
+      continue;
+    }
+    const int64_t work = (int64_t)nb * desc->heads_q;
+    if (!pk.fits(work) && (s = flush()) != SEER_OK) return s;
+    pk.add(r, nb, work);
+  }
+  return flush();
 }
 
 }  // extern "C"

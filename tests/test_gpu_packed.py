@@ -1,0 +1,73 @@
+"""Packed batches whose short sequences share launches: every count, index list
+and output equals, bit for bit, the calls on the sequences one by one (views of
+the same tensors), over sequence counts around the 64 of one launch, sequences
+on both sides of the sharing limits (128 blocks in the gate, 32 MiB of K and V
+in attention), workspaces that hold one or all of them, and every option."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+seer = pytest.importorskip("paper_2410_13276_amd")
+
+
+def _few(n):
+    return [(37 * x) % 300 for x in range(n)]  # some empty
+
+
+# (lengths, Hq, Hkv, D, dtype, block, kv_shared, gate options)
+CASES = [
+    ([1, 0, 0, 129], 4, 2, 128, "bf16", 64, False, dict(mode=seer.TOPK_FIXED, topk_k=3)),
+    (_few(63) + [64], 2, 1, 64, "bf16", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.4)),
+    (_few(150), 6, 2, 64, "bf16", 64, False, dict(mode=seer.THRESHOLD, threshold=0.05)),
+    ([8192, 8193, 700, 64, 8100, 2048], 8, 8, 128, "bf16", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.1)),
+    ([300, 4000, 64, 65], 72, 8, 64, "bf16", 64, False, dict(mode=seer.TOPK_FIXED, topk_k=5, rope_theta=1e4)),
+    ([16384, 16385, 130, 5000], 4, 2, 128, "bf16", 128, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.2)),
+    ([900, 129, 3, 2500], 4, 2, 128, "bf16", 64, True, dict(mode=seer.TOPK_RATIO, topk_ratio=0.3)),
+    ([900, 129, 3, 2500], 6, 2, 64, "bf16", 128, True, dict(mode=seer.TOPK_RATIO, topk_ratio=0.3)),
+    ([200, 1000, 64], 2, 1, 128, "f32", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.3)),
+    ([200, 1000, 64], 2, 1, 128, "f32", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.3, gate_dim=32)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_packed_equals_separate_calls(case):
+    lengths, Hq, Hkv, D, dtype, block, shared, kw = CASES[case]
+    print(f"[packed] case {case}", flush=True)
+    kw = dict(kw, block=block, kv_shared=shared)
+    dg = kw.pop("gate_dim", D)
+    gen = torch.Generator(device="cuda").manual_seed(100 + case)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cu = [0]
+    for n in lengths:
+        cu.append(cu[-1] + n)
+    q, k, v = (torch.randn(cu[-1], h, D, generator=gen, device="cuda").to(dt) for h in (Hq, Hkv, Hkv))
+    wq = torch.randn(Hq, D, dg, generator=gen, device="cuda") / dg ** 0.5
+    wk = torch.randn(Hkv, 3 * D, dg, generator=gen, device="cuda") / dg ** 0.5
+    singles = []
+    for b, n in enumerate(lengths):
+        if n:
+            qb, kb, vb = (t[cu[b]:cu[b + 1]].permute(1, 0, 2).unsqueeze(0) for t in (q, k, v))
+            m = seer.gate(qb, kb, wq, wk, dense_out=True, **kw)
+            o, lse = seer.bsattn(qb, kb, vb, m, want_lse=True)
+            singles.append((b, n, m, o, lse))
+    smallest = max(seer.gate_workspace_bytes(q[:n].permute(1, 0, 2).unsqueeze(0), k[:n].permute(1, 0, 2).unsqueeze(0), dg)
+                   for n in lengths if n)
+    for room in (None, smallest) if block == 64 else (None,):
+        mask = seer.alloc_varlen_mask(q, k, cu, block, shared, dense=True)
+        ws = None if room is None else torch.empty(room, dtype=torch.uint8, device="cuda")
+        seer.gate_varlen(q, k, wq, wk, cu, mask=mask, workspace=ws, **kw)
+        out = torch.full_like(q, float("nan"))
+        lse = torch.full((Hq * cu[-1],), float("nan"), device="cuda")
+        seer.bsattn_varlen(q, k, v, cu, mask, out=out, lse=lse)
+        i0 = 0
+        for b, n, m, o1, l1 in singles:
+            cnt, idx = mask.sequence(b)
+            nb = cnt.shape[1]
+            i0 = sum(mask.heads * (-(-x // block)) ** 2 for x in lengths[:b])
+            assert torch.equal(cnt, m.count[0])
+            keep = torch.arange(nb, device="cuda") < cnt.unsqueeze(-1)
+            assert torch.equal(idx.masked_fill(~keep, 0), m.idx[0].masked_fill(~keep, 0))
+            assert torch.equal(mask.dense[i0:i0 + mask.heads * nb * nb].view_as(m.dense[0]), m.dense[0])
+            assert torch.equal(out[cu[b]:cu[b + 1]].permute(1, 0, 2), o1[0])
+            assert torch.equal(lse[Hq * cu[b]:Hq * cu[b + 1]].view(Hq, n), l1[0])
