@@ -547,9 +547,14 @@ constexpr int kListChunk = 256;
 // row of a 131072-token mask), so that a row can be walked in another order.
 constexpr int kListWhole = 2048;
 
-// Two workgroups' worth of wavefronts per SIMD (<= 256 registers per lane) so
-// that one wavefront's softmax overlaps another's MFMA work.
-//
+// Wavefronts per SIMD, so that one's softmax overlaps another's MFMA work.  Head
+// dim 128 needs 210-230 registers per lane: two.  Head dim 64 has as much
+// softmax work per tile but half the MFMA work, and fits 168 registers: three
+// (4 x 16 heads of 4000 tokens, 12 blocks per row: attention 88 -> 79 us; 43161
+// tokens, 28 blocks: prefill 471 -> 439 us; launches that do not fill the GPU
+// within 1%; four would spill: 88 -> 120 us).  The split kernels need up to 196.
+constexpr int waves_per_simd(int head_dim, bool split) { return head_dim == 64 && !split ? 3 : 2; }
+
 // Pipeline per key tile n (one K and one V buffer, two barriers):
 //   S = K_n Q^T from LDS                  (V_n landing)
 //   wait + barrier A -> issue K_{n+1}     (V_n visible; K_n consumed)
@@ -583,7 +588,7 @@ constexpr int kListWhole = 2048;
 //
 // VAR: the rows of several sequences of a packed batch (decode_packed).
 template <int D, bool SPARSE, bool SPLIT, bool RAGGED, int NH = 1, bool VAR = false>
-__global__ __launch_bounds__(128 * NH) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(128 * NH) __attribute__((amdgpu_waves_per_eu(waves_per_simd(D, SPLIT), waves_per_simd(D, SPLIT))))
 void attn_fwd_bf16_kernel(LaunchArgs<VAR> ka) {
   using Lay = Bf16Layout<D>;
   constexpr int NW = 2 * NH;  // wavefronts
