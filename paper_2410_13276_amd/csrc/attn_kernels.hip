@@ -258,35 +258,6 @@ __device__ __forceinline__ RowList<SPARSE> make_list(const AttnArgs& a, const Ta
   return L;
 }
 
-// Online-softmax update of one 64-key tile held as S^T in s[0..1] (32 keys each);
-// converts s in place to unnormalised probabilities and returns the factor by
-// which the running output must be rescaled.
-__device__ __forceinline__ float softmax_tile(f32x16 (&s)[2], float& m_run, float& l_run,
-                                              float c, float& mloc) {
-  mloc = -INFINITY;
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) mloc = fmaxf(mloc, s[mt][e]);
-  mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-  const float m_new = fmaxf(m_run, mloc);
-  const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-  const float alpha = exp2f((m_run - m_use) * c);
-  const float mc = m_use * c;
-  float psum = 0.f;
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const float p = exp2f(fmaf(s[mt][e], c, -mc));
-      s[mt][e] = p;
-      psum += p;
-    }
-  l_run = l_run * alpha + psum;
-  m_run = m_new;
-  return alpha;
-}
-
 // Ground-truth epilogue of one query block (appendix A.1, Eq. 6 and the column
 // max after it).  rrow[j][t] holds the raw-score maximum of query t over key
 // tile j; sL2[t] = m_t c + log2(l_t) is the final softmax normaliser of query t
@@ -1161,23 +1132,83 @@ void attn_fwd_bf16_kernel(LaunchArgs<VAR> ka) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 kernel (v_mfma_f32_32x32x2_f32): same structure, no prefetch
+// fp32 kernel (v_mfma_f32_32x32x2_f32)
 // ---------------------------------------------------------------------------
+//
+// Bound by the fp32 MFMA rate (64 cycles per 32x32x2 step, 256 flop per clock
+// and CU): the decomposition keeps every SIMD's matrix core fed.  A workgroup
+// owns 64 queries, as in the bf16 kernel, but four wavefronts share a tile: two
+// query halves times two key halves, each wavefront with its own running
+// maximum, sum and output over its keys, merged through LDS at the row's end.
+// At head dim 128 a K and V tile fill 64 KiB of LDS, two workgroups per CU, so
+// four wavefronts per tile are two per SIMD (two per tile left one, which could
+// not hide its own loads and softmax).  Tiles reach LDS by direct loads, K of
+// the next tile under this tile's P.V product and V under its S product.
+//
+// Short launches (f32_shape): KG = 2 such groups take the row's tiles n = kg, kg +
+// KG, ... in step, each in its own LDS buffers; QS = 1 gives each query half its
+// own workgroup.
+//
+// Measured (attention alone): 32 / 8 heads of 128 at 4096 tokens, a quarter of
+// the tiles, 478 -> 314 us; dense 129 TF/s (the card's large fp32 product 152); 2
+// / 1 heads of 64 at 1024 tokens, half of the tiles, 47.8 -> 19 us.
+template <int D, int KG, int QS>
+struct F32Layout {
+  static constexpr int CPR = D / 4;         // 16-byte chunks per row
+  static constexpr int TILE = 64 * D;       // floats per K or V tile
+  static constexpr int LOADS = CPR / (2 * QS);  // direct loads per wavefront and tile
+  static constexpr int THREADS = 128 * QS * KG;
+  // K chunk c of row r sits at chunk c ^ (r % 16): the 16 rows of an operand
+  // read's pass hit 16 bank groups.  V chunk c at c ^ 8 ((r / 4) % 2): the two
+  // lane halves of a V read, rows 4 apart, hit different halves of the banks.
+  __device__ static int fk(int r) { return r & 15; }
+  __device__ static int fv(int r) { return 8 * ((r >> 2) & 1); }
+};
 
-template <int D>
-__global__ __launch_bounds__(128) void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
-  constexpr int KS = D + 4;  // LDS row stride of K (floats)
-  constexpr int VS = D;      // LDS row stride of V (floats)
-  __shared__ __attribute__((aligned(16))) float sK[64 * KS];
-  __shared__ __attribute__((aligned(16))) float sV[64 * VS];
-  __shared__ __attribute__((aligned(16))) float sL2[64];
+// One 16-byte direct load per lane from its own 64-bit address.
+__device__ __forceinline__ void dma16_at(uint32_t lds_base, const void* p) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(p) : "memory", "m0");
+}
+
+// A group's 2 QS wavefronts (w = 0, ..) load one 64-row tile; rows past `rows`
+// read the last one (finite data, masked or discarded later).
+template <int D, int QS, bool IS_V>
+__device__ __forceinline__ void load_tile_f32(uint32_t lds, const float* tile, int64_t ss, int w, int lane, int rows) {
+  using Lay = F32Layout<D, 1, QS>;
+#pragma unroll
+  for (int e = 0; e < Lay::LOADS; ++e) {
+    const int q = 64 * (2 * QS * e + w) + lane;
+    const int r = q / Lay::CPR;
+    const int gc = (q % Lay::CPR) ^ (IS_V ? Lay::fv(r) : Lay::fk(r));
+    dma16_at(lds + 1024u * (2 * QS * e + w), tile + min(r, rows - 1) * ss + 4 * gc);
+  }
+}
+
+// Wavefronts per SIMD: what LDS leaves room for; at head dim 64 three of them (two
+// 1-7% slower; four spill, faster on the longest launches only).
+constexpr int f32_waves(int head_dim, int kg) { return head_dim == 64 && kg == 1 ? 3 : 2; }
+
+template <int D, int KG, int QS>
+__global__ __launch_bounds__(128 * QS * KG) __attribute__((amdgpu_waves_per_eu(f32_waves(D, KG), f32_waves(D, KG))))
+void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
+  using Lay = F32Layout<D, KG, QS>;
+  constexpr int NP = 2 * KG;  // partial results per query: key halves x groups
+  __shared__ __attribute__((aligned(16))) float sT[KG][2 * Lay::TILE];
+  __shared__ float sM[NP][64], sS[NP][64];  // the partials' maxima and sums
+  __shared__ float sX[KG][64];              // ground truth: the upper key halves' tile maxima
+  __shared__ float sL2[64];
+  __shared__ int sEnd;
 
   const AttnArgs& a = ka.a;
   bool none;
-  const Task t = decode_task(ka.map, blockIdx.x, none);
+  // QS 1: workgroups 16 n + x and 16 n + 8 + x hold the two halves of task 8 n + x (one XCD)
+  const int wg = blockIdx.x;
+  const Task t = decode_task(ka.map, QS == 2 ? wg : (wg >> 4) * 8 + (wg & 7), none);
   if (none) return;
   const int tid = threadIdx.x;
-  const int wave = tid / 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int kg = wave / (2 * QS), wq = wave % (2 * QS);       // tile group, wavefront of the group
+  const int qh = QS == 2 ? wq / 2 : (wg >> 3) & 1, kh = wq % 2;  // query half, key half
   const int lane = tid % 64;
   const int hf = lane / 32;
   const int col = lane % 32;
@@ -1188,123 +1219,209 @@ __global__ __launch_bounds__(128) void attn_fwd_f32_kernel(LaunchArgs<false> ka,
   const float* vp = static_cast<const float*>(a.v.ptr) + t.b * a.v.sb + g * a.v.sh;
 
   const int S = a.seq_len;
-  const int qrow = 64 * t.i + 32 * wave + col;
-  const int qrow_c = min(qrow, S - 1);  // rows past the end read the last row, never stored
+  const int ql = 32 * qh + col;  // this lane's query of the block
   const int n_last = S - 64 * (a.n_blocks - 1);
   const bool ragged = n_last < 64;
-  f32x4 qf[D / 8];  // features 8u + 4hf .. +3 of this lane's query
+  f32x4 qf[D / 8];  // features 8u + 4hf .. +3 of this lane's query (rows past the end read the last, never stored)
 #pragma unroll
   for (int u = 0; u < D / 8; ++u)
-    qf[u] = *reinterpret_cast<const f32x4*>(qp + (int64_t)qrow_c * a.q.ss + 8 * u + 4 * hf);
+    qf[u] = *reinterpret_cast<const f32x4*>(qp + (int64_t)min(64 * t.i + ql, S - 1) * a.q.ss + 8 * u + 4 * hf);
 
   f32x16 acc[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = -INFINITY, l_run = 0.f, mc = 0.f;  // mc = m_run c, 0 while m_run is -inf
   const float c = ka.scale_log2;
 
+  // the row's tiles, up to the first entry that ends it
   RowList<true> sl;
   RowList<false> dl;
   int n_tiles;
   if (sparse) {
     sl = make_list<true>(a, t);
     n_tiles = sl.n;
+    if (tid == 0) sEnd = n_tiles;
+    __syncthreads();
+    for (int p = tid; p < n_tiles; p += Lay::THREADS)
+      if (!sl.ok(sl.at(p))) {
+        atomicMin(&sEnd, p);
+        break;
+      }
+    __syncthreads();
+    n_tiles = __builtin_amdgcn_readfirstlane(sEnd);
   } else {
     dl = make_list<false>(a, t);
     n_tiles = dl.n;
   }
-  const bool pool = a.gt != nullptr;  // the launcher enables it for dense rows only
+  auto entry = [&](int n) -> int {
+    return n < n_tiles ? __builtin_amdgcn_readfirstlane(sparse ? sl.at(n) : dl.at(n)) : -1;
+  };
+  const bool pool = QS == 2 && a.gt != nullptr;  // the launcher enables it for dense rows only
   const int64_t trow = ((int64_t)t.b * a.heads_q + t.h) * a.n_blocks + t.i;
   float* const rrow = pool ? a.pool_r + trow * a.n_blocks * 64 : nullptr;
-  for (int n = 0; n < n_tiles; ++n) {
-    const int j = sparse ? sl.at(n) : dl.at(n);
-    if (!(sparse ? sl.ok(j) : dl.ok(j))) break;
-    __syncthreads();
-    constexpr int CPR = D / 4;
-#pragma unroll
-    for (int e = 0; e < 64 * CPR / 128; ++e) {
-      const int q = tid + 128 * e;
-      const int key = q / CPR, cc = q % CPR;
-      const int krow = min(64 * j + key, S - 1);  // clamped inside the last tile
-      *reinterpret_cast<f32x4*>(sK + key * KS + 4 * cc) =
-          *reinterpret_cast<const f32x4*>(kp + (int64_t)krow * a.k.ss + 4 * cc);
-      *reinterpret_cast<f32x4*>(sV + key * VS + 4 * cc) =
-          *reinterpret_cast<const f32x4*>(vp + (int64_t)krow * a.v.ss + 4 * cc);
-    }
-    __syncthreads();
 
-    f32x16 s[2];
+  float* const sK = sT[kg];
+  float* const sV = sT[kg] + Lay::TILE;
+  const uint32_t sK_a = lds_addr(sK), sV_a = lds_addr(sV);
+  auto load_k = [&](int j) {
+    load_tile_f32<D, QS, false>(sK_a, kp + 64 * (int64_t)j * a.k.ss, a.k.ss, wq, lane, min(64, S - 64 * j));
+  };
+  auto load_v = [&](int j) {
+    load_tile_f32<D, QS, true>(sV_a, vp + 64 * (int64_t)j * a.v.ss, a.v.ss, wq, lane, min(64, S - 64 * j));
+  };
+  // operand reads: K row 32 kh + col, chunks 2u + hf; V rows 32 kh + 8 (e / 4) +
+  // 4 hf + e % 4, feature 32 dt + col (its swizzle swaps even and odd dt for hf = 1)
+  int koff[8];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
+  for (int u = 0; u < 8; ++u) koff[u] = (32 * kh + col) * D + 4 * ((2 * u + hf) ^ Lay::fk(col));
+  const int vbase = (32 * kh + 4 * hf) * D + col;
+  const int voff[2] = {vbase + 32 * hf, vbase + 32 * (1 - hf)};
+
+  int j = entry(kg);
+  if (j >= 0) {
+    load_k(j);
+    load_v(j);
+  }
+  wait_loads();
+  __syncthreads();
+  for (int n0 = 0; n0 < n_tiles; n0 += KG) {  // every group runs every step (the barriers are the workgroup's)
+    const bool on = j >= 0;
+    const int jn = entry(n0 + KG + kg);
+    f32x16 s;
+    float mloc = -INFINITY;
+    if (on) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) s[mt][e] = 0.f;
+      for (int e = 0; e < 16; ++e) s[e] = 0.f;
+      auto read_k = [&](int u) { return *reinterpret_cast<const f32x4*>(sK + koff[u % 8] + 64 * (u / 8)); };
+      f32x4 k0 = read_k(0), k1 = read_k(1);  // read two steps (eight MFMAs) ahead of their use
 #pragma unroll
       for (int u = 0; u < D / 8; ++u) {
-        const f32x4 kf = *reinterpret_cast<const f32x4*>(sK + (32 * mt + col) * KS + 8 * u + 4 * hf);
+        const f32x4 kf = k0;
+        k0 = k1;
+        if (u + 2 < D / 8) k1 = read_k(u + 2);
 #pragma unroll
-        for (int vv = 0; vv < 4; ++vv)
-          s[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[vv], qf[u][vv], s[mt], 0, 0, 0);
+        for (int vv = 0; vv < 4; ++vv) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[vv], qf[u][vv], s, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const bool diag = a.causal && j == t.i;
+      const bool tail = ragged && !a.causal && j == a.n_blocks - 1;
+      if (diag || tail) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int kl = 32 * kh + 8 * (e / 4) + 4 * hf + (e % 4);
+          if ((diag && kl > ql) || (tail && kl >= n_last)) s[e] = -INFINITY;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mloc = fmaxf(mloc, s[e]);
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mloc), __float_as_uint(mloc), false, false);
+      mloc = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      if (pool && kh == 1 && hf == 0) sX[kg][ql] = mloc;
+    }
+    wait_loads();
+    __syncthreads();  // K consumed, V visible
+    if (jn >= 0) load_k(jn);
+    if (on) {
+      if (pool && kh == 0 && hf == 0) rrow[(int64_t)j * 64 + ql] = fmaxf(mloc, sX[kg][ql]);  // Eq. 5
+      // the running maximum moves (and O, l are rescaled) only when some lane's
+      // tile maximum exceeds it by more than 2^8 in the exp2 domain
+      if (__ballot((mloc - m_run) * c > 8.0f) != 0) {
+        const float m_new = fmaxf(m_run, mloc);
+        const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * c);
+        m_run = m_new;
+        mc = m_run == -INFINITY ? 0.f : m_run * c;
+        l_run *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[dt][e] *= alpha;
+      }
+      float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], c, -mc));
+        ps[e % 4] += s[e];
+      }
+      l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+      // O^T += V^T P^T one key pair per MFMA: lane half hf supplies key 8 (e / 4) +
+      // 4 hf + e % 4 of the wavefront's half, whose probability this lane already
+      // holds; the feature tiles alternate, so consecutive MFMAs are independent,
+      // and the V operands are read one key pair ahead
+      float vn[D / 32];
+      auto read_v = [&](int e, float (&v)[D / 32]) {
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt) v[dt] = sV[voff[dt % 2] + (8 * (e / 4) + e % 4) * D + 64 * (dt / 2)];
+      };
+      read_v(0, vn);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        float v[D / 32];
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt) v[dt] = vn[dt];
+        if (e + 1 < 16) read_v(e + 1, vn);
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[dt], s[e], acc[dt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    const bool diag = a.causal && j == t.i;
-    const bool tail = ragged && !a.causal && j == a.n_blocks - 1;
-    if (diag || tail) {
-      const int ql = 32 * wave + col;
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int kl = 32 * mt + 8 * (e / 4) + 4 * hf + (e % 4);
-          if ((diag && kl > ql) || (tail && kl >= n_last)) s[mt][e] = -INFINITY;
-        }
-    }
-    float rmax;
-    const float alpha = softmax_tile(s, m_run, l_run, c, rmax);
-    if (pool && hf == 0) rrow[(int64_t)j * 64 + 32 * wave + col] = rmax;  // Eq. 5
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[dt][e] *= alpha;
-    // O^T += V^T P^T one key pair per MFMA: lane half hf supplies key
-    // 32mt + 8(e/4) + 4hf + e%4, whose probability this lane already holds
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int key = 32 * mt + 8 * (e / 4) + 4 * hf + (e % 4);
-          acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(sV[key * VS + 32 * dt + col], s[mt][e],
-                                                         acc[dt], 0, 0, 0);
-        }
+    wait_loads();
+    __syncthreads();  // V consumed, K visible
+    if (jn >= 0) load_v(jn);
+    j = jn;
   }
 
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  const float inv = (l_tot > 0.f) ? 1.0f / l_tot : 0.f;
-  float* op = static_cast<float*>(a.o) + t.b * a.osb + t.h * a.osh + (int64_t)qrow * a.oss;
-  if (qrow < S) {
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        f32x4 o4;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o4[r] = acc[dt][4 * jj + r] * inv;
-        *reinterpret_cast<f32x4*>(op + 32 * dt + 8 * jj + 4 * hf) = o4;
-      }
+  // merge: each partial rescaled to the query's common maximum, summed over LDS
+  const int part = 2 * kg + kh;
+  const float l_half = l_run + __shfl_xor(l_run, 32);
+  if (hf == 0) {
+    sM[part][ql] = m_run;
+    sS[part][ql] = l_half;
   }
-  if (a.lse && hf == 0 && qrow < S) {
-    const float lse = (l_tot > 0.f) ? m_run * a.scale + __logf(l_tot) : -INFINITY;
-    a.lse[((int64_t)t.b * a.heads_q + t.h) * (int64_t)S + qrow] = lse;
+  __syncthreads();
+  float m_all = -INFINITY;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) m_all = fmaxf(m_all, sM[p][ql]);
+  auto weight = [&](float m) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_all) * c); };
+  float l_tot = 0.f;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) l_tot += sS[p][ql] * weight(sM[p][ql]);
+  const float w = weight(m_run) * (l_tot > 0.f ? 1.0f / l_tot : 0.f);
+  // (wavefront wq of a group stages in its quarter of the group's tile buffers,
+  // whose tiles are all consumed; chunks swizzled by query as K's are by row)
+  float* const mine = sT[kg] + wq * 32 * D;
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      f32x4 o4;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o4[r] = acc[dt][4 * jj + r] * w;
+      *reinterpret_cast<f32x4*>(mine + col * D + 4 * ((8 * dt + 2 * jj + hf) ^ Lay::fk(col))) = o4;
+    }
+  const int qrow = 64 * t.i + ql;
+  if (kg == 0 && kh == 0 && hf == 0) {
+    if (a.lse && qrow < S)
+      a.lse[((int64_t)t.b * a.heads_q + t.h) * a.seq_len + qrow] =
+          (l_tot > 0.f) ? m_all * a.scale + __logf(l_tot) : -INFINITY;
+    if (pool) sL2[ql] = (l_tot > 0.f && qrow < S) ? m_all * c + __log2f(l_tot) : INFINITY;
   }
-  if (pool) {
-    if (hf == 0) sL2[32 * wave + col] = (l_tot > 0.f && qrow < S) ? m_run * c + __log2f(l_tot) : INFINITY;
-    __threadfence_block();
-    __syncthreads();
-    pool_epilogue(rrow, sL2, c, n_tiles, a.n_blocks, a.gt + trow * a.n_blocks, tid, 128);
+  wait_loads();  // (ground truth: the row-max stores have completed)
+  __syncthreads();
+  float* op = static_cast<float*>(a.o) + t.b * a.osb + t.h * a.osh;
+#pragma unroll
+  for (int e = 0; e < 32 * QS * Lay::CPR / Lay::THREADS; ++e) {
+    const int x = tid + Lay::THREADS * e;
+    const int q = x / Lay::CPR, ch = x % Lay::CPR;  // (q counts the workgroup's queries)
+    const int row = 64 * t.i + (QS == 2 ? q : 32 * qh + q);
+    f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      o4 += *reinterpret_cast<const f32x4*>(sT[p / 2] + (2 * (q / 32) + p % 2) * 32 * D + (q % 32) * D + 4 * (ch ^ Lay::fk(q % 32)));
+    if (row < S) *reinterpret_cast<f32x4*>(op + (int64_t)row * a.oss + 4 * ch) = o4;
   }
+  if (pool) pool_epilogue(rrow, sL2, c, n_tiles, a.n_blocks, a.gt + trow * a.n_blocks, tid, Lay::THREADS);
 }
 
 // ---------------------------------------------------------------------------
@@ -1436,6 +1553,18 @@ int64_t split_slots_per_head(int n_blocks, int w) {
   return n_blocks + w * q * (q - 1) / 2 + r * q;
 }
 
+// Tile groups and query halves per workgroup of the fp32 kernel for a call of so
+// many (batch, head, query block) rows.  Up to 256 rows leave CUs idle: a
+// workgroup per query half, two tile groups each (rows of 16-64 blocks, dense,
+// head dim 64 / 128, us: 128 rows 84 -> 47 / 144 -> 89; 256 rows 162 -> 118 / 281
+// -> 194).  Up to 768, two tile groups balance the rows better over one round of
+// workgroups (512 rows 213 -> 162 / 392 -> 302); from 1024 on the workgroups do
+// that themselves, and two per CU hide each other's barriers (2048 rows: 559
+// against 611 / 1080 against 1142).
+F32Shape f32_shape(int64_t rows) {
+  return F32Shape{rows <= 768 ? 2 : 1, rows <= 256 ? 1 : 2};
+}
+
 // Workgroups of a kernel that the GPU holds at once (compute units x
 // occupancy), queried once per device and kernel and kept for the process.
 static int resident_capacity(const void* fn, int threads) {
@@ -1539,6 +1668,13 @@ static int kv_heads_per_wg(const AttnArgs& a) {
   for (int nh = 4; nh >= 2; nh /= 2)
     if (nh <= a.heads_per_wg && G % nh == 0) return nh;
   return 1;
+}
+
+template <int D>
+static void launch_f32(const LaunchArgs<false>& ka, int qs, unsigned total, hipStream_t s, int* count, bool sparse) {
+  if (ka.a.f32_groups == 1) SEER_LAUNCH((attn_fwd_f32_kernel<D, 1, 2>), dim3(total), dim3(256), s, count, ka, (int)sparse);
+  else if (qs == 2) SEER_LAUNCH((attn_fwd_f32_kernel<D, 2, 2>), dim3(total), dim3(512), s, count, ka, (int)sparse);
+  else SEER_LAUNCH((attn_fwd_f32_kernel<D, 2, 1>), dim3(2 * total), dim3(256), s, count, ka, (int)sparse);
 }
 
 template <int D, bool SPARSE, bool RAGGED>
@@ -1683,8 +1819,10 @@ static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count) 
       return hipErrorInvalidValue;
     }
   } else {
-    if (a.head_dim == 128) SEER_LAUNCH(attn_fwd_f32_kernel<128>, grid, block, s, count, ka, (int)sparse);
-    else if (a.head_dim == 64) SEER_LAUNCH(attn_fwd_f32_kernel<64>, grid, block, s, count, ka, (int)sparse);
+    // (the ground truth's column maxima need a row's 64 queries in one workgroup)
+    const int qs = pool ? 2 : a.f32_halves;
+    if (a.head_dim == 128) launch_f32<128>(ka, qs, grid.x, s, count, sparse);
+    else if (a.head_dim == 64) launch_f32<64>(ka, qs, grid.x, s, count, sparse);
     else return hipErrorInvalidValue;
   }
   return done();

@@ -133,6 +133,8 @@ struct AttnArgs {
   int batch_wgs;                // workgroups per batch (0: the resident capacity)
   int walk_classes;             // unsplit sparse rows walk their blocks by residue classes
                                 // mod this (a power of two up to 16; 1: ascending)
+  int f32_groups, f32_halves;   // tile groups and query halves per workgroup of the fp32 kernel
+                                // (f32_shape of the whole call, also where it runs as several launches)
   float* part_lse;              // [slots][64] log2-domain log-sum-exp of each partial
   uint16_t* part_o;             // [slots][64][D] bf16 partial outputs, normalised
 };
@@ -207,6 +209,10 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t s, int* count = nullptr);
 hipError_t launch_attn_packed(const AttnArgs& a, const PackedSeqs& seqs, hipStream_t s);
 // Whether a sequence of n_blocks tiles joins such a launch.
 bool attn_packs(const AttnArgs& a, int n_blocks);
+struct F32Shape {
+  int groups, halves;
+};
+F32Shape f32_shape(int64_t rows);
 // Split geometry: the key-range width in blocks for a launch (0 when the shape
 // does not split) and the partial slots per (batch, head) for a range width.
 int split_width(int n_blocks, int head_dim, bool causal, bool bf16, bool want, int width);

@@ -277,6 +277,9 @@ seer::AttnArgs attn_args(const seer_attn_desc* desc, int32_t causal, float sm_sc
   a.batch_min_blocks = 2048;
   a.batch_wgs = 0;
   a.walk_classes = 4;  // measured: 131072 tokens 17.1 -> 14.4-14.7 ms, 65536 (GQA 7:1) 7.56 -> 7.25 ms
+  const seer::F32Shape f = seer::f32_shape((int64_t)a.batch * a.heads_q * a.n_blocks);
+  a.f32_groups = f.groups;
+  a.f32_halves = f.halves;
   a.part_lse = nullptr;
   a.part_o = nullptr;
   return a;

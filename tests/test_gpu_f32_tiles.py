@@ -1,0 +1,54 @@
+"""The fp32 attention kernel's tile groups and key halves against the fp64 oracle:
+row counts on both sides of each rule (256 and 768 rows), rows of fewer tiles than
+groups, partial last tiles, empty rows,
+lists that end early, with and without causality; the ground truth's map and the
+dense outputs equal whatever the KV groups per launch.  Bar: 1e-4 max-abs (the
+fp32 bar of the other tests; measured 5e-7)."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import ATOL_F32, lists_from_dense, small_inputs, stable_seed, to_device, upload_mask
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+seer = pytest.importorskip("paper_2410_13276_amd")
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,Hq,Hkv,S,D", [(1, 2, 1, 1, 64), (1, 2, 1, 130, 64), (1, 2, 1, 1000, 64), (1, 16, 4, 1024, 64),
+                                          (1, 16, 4, 1025, 64), (2, 24, 8, 1024, 64), (1, 49, 7, 1000, 64),
+                                          (1, 2, 1, 65, 128), (1, 16, 4, 1024, 128), (1, 16, 4, 1030, 128),
+                                          (1, 26, 2, 1900, 128)])
+def test_f32_sparse_and_dense(B, Hq, Hkv, S, D, causal):
+    print(f"[f32] {B} {Hq}/{Hkv} {S} {D} {causal}", flush=True)
+    seed = stable_seed("f32", B, Hq, S, D, causal)
+    _, q, k, v, _, _ = small_inputs(B, Hq, Hkv, S, D, "f32", seed=seed)
+    nb = -(-S // 64)
+    rng = np.random.default_rng(seed)
+    m = (rng.random((B, Hq, nb, nb)) < 0.35).astype(np.uint8)
+    m[:, 0, nb // 2] = 0  # an empty row
+    if causal:
+        m *= np.tril(np.ones((nb, nb), np.uint8))
+    qd, kd, vd = to_device(q), to_device(k), to_device(v)
+    cnt, idx = lists_from_dense(m)
+    if causal and nb > 1:  # an entry past the diagonal ends the row, whatever follows
+        cnt[0, 1, 0], idx[0, 1, 0, 0] = 2, 0
+        idx[0, 1, 0, 1] = nb - 1
+        m[0, 1, 0] = 0
+        m[0, 1, 0, 0] = 1
+    o, lse = seer.bsattn(qd, kd, vd, upload_mask(cnt, idx), causal=causal, want_lse=True, out=torch.full_like(qd, 9.0))
+    O, L = oracle.attn(q, k, v, mask=m, causal=causal)
+    ref, lref = O.reshape(B, Hq, nb * 64, D)[:, :, :S], L.reshape(B, Hq, nb * 64)[:, :, :S]
+    assert float(np.abs(o.cpu().numpy() - np.nan_to_num(ref)).max()) <= ATOL_F32
+    got = lse.cpu().numpy()
+    fin = np.isfinite(lref)
+    assert np.array_equal(fin, np.isfinite(got)) and bool((np.abs(got[fin] - lref[fin]) <= 1e-4).all())
+    od, _ = seer.dense_attn(qd, kd, vd, causal=causal)
+    O, _ = oracle.attn(q, k, v, causal=causal)
+    assert float(np.abs(od.cpu().numpy() - O.reshape(B, Hq, nb * 64, D)[:, :, :S]).max()) <= ATOL_F32
+    og, _, gt = seer.attn_gt(qd, kd, vd, causal=causal)
+    ws = torch.empty(seer.attn_gt_workspace_bytes(qd, kd, vd, 1), dtype=torch.uint8, device="cuda")
+    o1, _, gt1 = seer.attn_gt(qd, kd, vd, causal=causal, workspace=ws)  # one KV group per launch
+    assert torch.equal(og, od) and torch.equal(o1, od) and torch.equal(gt1, gt)
