@@ -119,6 +119,23 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
   const int r = t / (TPR * RS);
   const int blk = chunk * R + r;
 
+  const int j = t % DG;
+  const int r0 = t / DG;  // GEMV rows r0, r0 + 256/DG, ...
+  constexpr int RSTEP = 256 / DG;
+  // A thread's GEMV reads a column of W in order; kAhead of its elements are in
+  // flight at a time, the first ones under the pooling.  With a few at a time the
+  // chain of dependent L2 reads (96 of 4 for K) took most of a short launch,
+  // whose few workgroups cannot hide it (2048 tokens, 32 query / 8 KV heads of
+  // 128: 20.6 -> 15.4 us; 8192: 31.9 -> 26.9; 64 ahead spill), and some of a
+  // long one (50001: 119 -> 114, 131072: 297 -> 288; 32 ahead no faster).
+  constexpr int kAhead = RS > 1 ? 32 : 16;
+  static_assert(WIDTH % kAhead == 0, "the weights are read in whole steps");
+  float wn[kAhead];
+  auto load_w = [&](int cc) {
+#pragma unroll
+    for (int e = 0; e < kAhead; ++e) wn[e] = W[(int64_t)(cc + e) * DG + j];
+  };
+  load_w(0);
   if (blk < nb) {
     float sum[EPL], mx[EPL], mn[EPL];
 #pragma unroll
@@ -130,8 +147,7 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
     const T* base = x + (int64_t)blk * BLK * ss + c * EPL;
     const int nrow = min(BLK, seq_len - blk * BLK);  // the last block may be partial
     const int row_end = min(nrow, (rs + 1) * (BLK / RS));
-#pragma unroll 8
-    for (int row = rs * (BLK / RS); row < row_end; ++row) {
+    auto take = [&](int row) {
       float v[EPL];
       Load16<T>::get(base + row * ss, v);
 #pragma unroll
@@ -142,6 +158,14 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
           mn[e] = fminf(mn[e], v[e]);
         }
       }
+    };
+    const int row0 = rs * (BLK / RS);
+    if (RS > 1 && row_end - row0 == BLK / RS) {  // (16 rows in flight per thread)
+#pragma unroll 16
+      for (int u = 0; u < BLK / RS; ++u) take(row0 + u);
+    } else {
+#pragma unroll 8
+      for (int row = row0; row < row_end; ++row) take(row);
     }
     // RS = 1: the pooled row; otherwise the range's raw sum, maximum, minimum
     float* prow = smem + (r * RS + rs) * WIDTH + c * EPL;
@@ -191,18 +215,11 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
     __syncthreads();
   }
 
-  // GEMV: out[r][j] = sum_c pooled[r][c] * W[c][j]
-  const int j = t % DG;
-  const int r0 = t / DG;  // rows r0, r0 + 256/DG, ...
-  constexpr int RSTEP = 256 / DG;
+  // GEMV: out[r][j] = sum_c pooled[r][c] * W[c][j], summed in the order of c
   float acc[RPT];
 #pragma unroll
   for (int q = 0; q < RPT; ++q) acc[q] = 0.f;
-#pragma unroll 2
-  for (int cc = 0; cc < WIDTH; cc += 4) {
-    float w[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) w[e] = W[(int64_t)(cc + e) * DG + j];
+  auto step4 = [&](int cc, const float* w) {
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
       const f32x4 p = *reinterpret_cast<const f32x4*>(smem + (r0 + q * RSTEP) * PSTR + cc);
@@ -211,6 +228,15 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
       acc[q] = fmaf(p[2], w[2], acc[q]);
       acc[q] = fmaf(p[3], w[3], acc[q]);
     }
+  };
+#pragma unroll 1
+  for (int cc = 0; cc < WIDTH; cc += kAhead) {
+    float w[kAhead];
+#pragma unroll
+    for (int e = 0; e < kAhead; ++e) w[e] = wn[e];
+    if (cc + kAhead < WIDTH) load_w(cc + kAhead);
+#pragma unroll
+    for (int e = 0; e < kAhead; e += 4) step4(cc + e, w + e);
   }
   if (rope_base > 0.0) {
     // Block-level RoPE (section 3.1): rotate plane (d, d + DG/2) of the row of
