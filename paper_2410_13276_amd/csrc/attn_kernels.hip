@@ -1255,8 +1255,14 @@ void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
     dl = make_list<false>(a, t);
     n_tiles = dl.n;
   }
-  auto entry = [&](int n) -> int {
-    return n < n_tiles ? __builtin_amdgcn_readfirstlane(sparse ? sl.at(n) : dl.at(n)) : -1;
+  // The list entry of position n (any n: the row's index array holds mask_blocks
+  // of them) and the tile it stands for, -1 past the end.  The entry's wait would
+  // also drain the tile loads in flight, so the loop loads it under S and uses it
+  // only after the wait that S's end needs anyway.
+  auto entry = [&](int n) -> uint32_t { return sparse ? sl.idx[min(n >> sl.sh, a.mask_blocks - 1)] : 0u; };
+  auto tile_of = [&](int n, uint32_t e) -> int {
+    const int jj = sparse ? ((int)__builtin_amdgcn_readfirstlane(e) << sl.sh) + (n & sl.sh) : dl.lo + n;
+    return n < n_tiles ? jj : -1;
   };
   const bool pool = QS == 2 && a.gt != nullptr;  // the launcher enables it for dense rows only
   const int64_t trow = ((int64_t)t.b * a.heads_q + t.h) * a.n_blocks + t.i;
@@ -1279,7 +1285,7 @@ void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
   const int vbase = (32 * kh + 4 * hf) * D + col;
   const int voff[2] = {vbase + 32 * hf, vbase + 32 * (1 - hf)};
 
-  int j = entry(kg);
+  int j = tile_of(kg, entry(kg));
   if (j >= 0) {
     load_k(j);
     load_v(j);
@@ -1288,7 +1294,7 @@ void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
   __syncthreads();
   for (int n0 = 0; n0 < n_tiles; n0 += KG) {  // every group runs every step (the barriers are the workgroup's)
     const bool on = j >= 0;
-    const int jn = entry(n0 + KG + kg);
+    const uint32_t en = entry(n0 + KG + kg);
     f32x16 s;
     float mloc = -INFINITY;
     if (on) {
@@ -1322,6 +1328,7 @@ void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
     }
     wait_loads();
     __syncthreads();  // K consumed, V visible
+    const int jn = tile_of(n0 + KG + kg, en);
     if (jn >= 0) load_k(jn);
     if (on) {
       if (pool && kh == 0 && hf == 0) rrow[(int64_t)j * 64 + ql] = fmaxf(mloc, sX[kg][ql]);  // Eq. 5
