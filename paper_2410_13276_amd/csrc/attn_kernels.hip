@@ -58,10 +58,11 @@ struct Task {
 //  - within an XCD, query-block rows run heaviest first (i descending) with
 //    the query heads of the group adjacent (they read the same K/V).
 // Where gpp does not divide the groups or R the blocks, the phases are rounded
-// up and the workgroups without a task end at once.  Each phase starts
-// its residues one XCD further, so that many phases of few blocks use every XCD.  Measured at 50001
-// tokens (782 blocks, 32 query / 8 KV heads, TopK 0.15): 4.72 ms when such
-// counts ran every head's rows interleaved over all XCDs, 3.5 ms in this order.
+// up and the workgroups without a task end at once.  Each phase starts its
+// residues one XCD further, so that many phases of few blocks use every XCD.
+// Measured at 50001 tokens (782 blocks, 32 query / 8 KV heads, TopK 0.15): 4.72
+// ms when such counts ran every head's rows interleaved over all XCDs, 3.3-3.5
+// ms in this order.
 // (The launch's first instructions are this decode, alone on its critical path:
 // its divisions multiply by reciprocals formed on the host.)
 struct Divisor {
@@ -1150,8 +1151,8 @@ void attn_fwd_bf16_kernel(LaunchArgs<VAR> ka) {
 // own workgroup.
 //
 // Measured (attention alone): 32 / 8 heads of 128 at 4096 tokens, a quarter of
-// the tiles, 478 -> 314 us; dense 129 TF/s (the card's large fp32 product 152); 2
-// / 1 heads of 64 at 1024 tokens, half of the tiles, 47.8 -> 19 us.
+// the tiles, 478 -> 300 us; dense 129 TF/s (the card's large fp32 product 152); 2
+// / 1 heads of 64 at 1024 tokens, half of the tiles, 47.8 -> 17 us.
 template <int D, int KG, int QS>
 struct F32Layout {
   static constexpr int CPR = D / 4;         // 16-byte chunks per row
