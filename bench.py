@@ -622,7 +622,7 @@ def main() -> int:
 
     active_flops = flops_tile * active
     D = w.head_dim
-    attn_kernel = f"attn_fwd_bf16_kernel<{D}, true, false, {'true' if w.seq_len % 64 else 'false'}, 1>"
+    attn_kernel = f"attn_fwd_bf16_kernel<{D}, true, false, {'true' if w.seq_len % 64 else 'false'}, 1, false>"
     attn_tflops = active_flops / (attn_ms * 1e-3) / 1e12
     # launches of the attention kernel one seer_bsattn call makes (the library's own count)
     launches = seer.attn_launches(qd, kd, vd, mask)
