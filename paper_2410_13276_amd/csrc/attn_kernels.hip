@@ -1508,6 +1508,15 @@ __global__ __launch_bounds__(256) void split_bounds_kernel(AttnArgs a) {
 // groups' unequal work no longer leaves half the XCDs idle at the end; 8k and
 // 32k shapes (4 and 16 MiB per group) ran the same with budgets of 32 and 64 MiB,
 // and slower with 16 or less.
+// Rows of a mask shared by each group (mask_kv) can differ widely in length from
+// group to group (thresholds per KV head), which idles XCDs where a phase gives
+// each group some of them.  There a block count that R does not divide goes one
+// group at a time: 32698 tokens, 28 / 4 heads, shares of 5-40% per group, a
+// prefill 2.31 -> 1.95 ms (2.11 with the rows of all groups interleaved).
+// (Masks per head average over a group's heads; one group at a time measured
+// 0.95-1.05x there, the most a call lost to the interleaved rows 5.6%: 19000
+// tokens, 12 / 4 heads, shares of 5-40% per head, 368 -> 390 us, 412 one group
+// at a time, against gains of 1.1-1.6x on most lengths.)
 constexpr double kPhaseBudget = 32.0 * 1024.0 * 1024.0;
 
 static Divisor divisor(int d) {
@@ -1526,6 +1535,7 @@ static TaskMap make_map(const AttnArgs& a) {
   for (int rsh = 0; rsh <= 3; ++rsh) {
     const int gpp = 8 >> rsh, R = 1 << rsh;
     if (gpp > 1 && gpp * kv_bytes > kPhaseBudget) continue;
+    if (gpp > 1 && a.count && a.mask_kv && a.n_blocks % R != 0) continue;  // see above
     const int tpp = ((a.n_blocks + R - 1) / R) * G;
     const int64_t total = (int64_t)((m.groups + gpp - 1) / gpp) * 8 * tpp;
     if (total >= fewest) continue;
