@@ -40,3 +40,24 @@ def test_every_row_once(B, Hq, Hkv, seq):
             if nb <= 300:
                 od1, _ = seer.dense_attn(qs, ks, vs, out=torch.empty_like(qs).contiguous())
                 assert torch.equal(od[b:b + 1, hs].view(torch.int16), od1.view(torch.int16))
+
+
+# one group at a time (261 and 523 blocks, no multiple of the XCDs per group) and all groups at once (130 blocks)
+@pytest.mark.parametrize("Hq,Hkv,seq", [(16, 8, 16700), (4, 2, 33409), (8, 8, 8320)])
+def test_every_row_of_a_shared_mask_once(Hq, Hkv, seq):
+    print(f"[task order] shared mask {Hq}/{Hkv} {seq}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(seq)
+    q, k, v = (torch.randn(1, h, seq, 128, generator=gen, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    nb, G = -(-seq // 64), Hq // Hkv
+    i = torch.arange(nb, device="cuda")
+    keep = torch.rand(1, Hkv, nb, nb, generator=gen, device="cuda") < 4.0 / nb
+    dense = ((keep | (i[None, :] == i[:, None])) & (i[None, :] <= i[:, None])).to(torch.uint8)
+    mask = seer.mask_from_dense(dense, kv_shared=True)
+    o = torch.full_like(q, float("nan"))
+    seer.bsattn(q, k, v, mask, out=o)
+    for g in range(Hkv):
+        hs = slice(g * G, g * G + G)
+        m = seer.BlockMask(count=mask.count[:, g:g + 1].contiguous(), idx=mask.idx[:, g:g + 1].contiguous(), kv_shared=True)
+        qs = q[:, hs].contiguous()
+        o1, _ = seer.bsattn(qs, k[:, g:g + 1], v[:, g:g + 1], m)
+        assert torch.equal(o[:, hs].view(torch.int16), o1.view(torch.int16))
