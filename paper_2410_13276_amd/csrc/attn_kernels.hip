@@ -430,8 +430,17 @@ struct Bf16Layout {
 // Issued through inline assembly so that the compiler does not add
 // conservative vmcnt waits in front of every LDS read; the kernel waits for
 // its own loads explicitly (wait_loads) before the barrier that publishes them.
+//
+// The compiler adds no wait states inside or around inline assembly.  gfx950
+// wants one between a scalar write of M0 and the load that uses it, and five
+// between a vector write of an SGPR (v_readlane of a spilled base) and a vector
+// memory instruction that reads it.  Moving the base onto itself is both: M0's
+// wait state, and a base last written by the scalar unit (131072 tokens, TopK
+// 0.1: 15.13 ms a prefill, 15.35 with five wait states in front of every load).
 __device__ __forceinline__ void dma16(uint32_t lds_base, const void* base, uint32_t voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff), "s"(base)
+  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %0\n\tglobal_load_lds_dwordx4 %2, %0"
+               : "+s"(base)
+               : "s"(lds_base), "v"(voff)
                : "memory", "m0");
 }
 
@@ -1166,9 +1175,10 @@ struct F32Layout {
   __device__ static int fv(int r) { return 8 * ((r >> 2) & 1); }
 };
 
-// One 16-byte direct load per lane from its own 64-bit address.
+// One 16-byte direct load per lane from its own 64-bit address (s_nop: M0's wait state, see dma16).
 __device__ __forceinline__ void dma16_at(uint32_t lds_base, const void* p) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(p) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(p)
+               : "memory", "m0");
 }
 
 // A group's 2 QS wavefronts (w = 0, ..) load one 64-row tile; rows past `rows`
