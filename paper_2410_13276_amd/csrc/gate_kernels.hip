@@ -362,10 +362,9 @@ static hipError_t pool_proj_op(int op, const PoolProjArgs& a, const PackedSeqs* 
   }
   if constexpr (PoolTiling<T, D, DG, 4>::ok) {
     if (rs == 4) return op == 2 ? pool_proj_launch_packed<T, D, DG, 4>(a, *p, s) : pool_proj_launch_rs<T, D, DG, 4>(a, s);
-  } else if (op == 2) {
-    return pool_proj_launch_packed<T, D, DG, 1>(a, *p, s);
   }
-  return op == 2 ? hipErrorInvalidValue : pool_proj_launch_rs<T, D, DG, 1>(a, s);
+  if (rs != 1) return hipErrorInvalidValue;
+  return op == 2 ? pool_proj_launch_packed<T, D, DG, 1>(a, *p, s) : pool_proj_launch_rs<T, D, DG, 1>(a, s);
 }
 
 template <typename T, int D>

@@ -27,6 +27,12 @@ CASES = [
     ([900, 129, 3, 2500], 6, 2, 64, "bf16", 128, True, dict(mode=seer.TOPK_RATIO, topk_ratio=0.3)),
     ([200, 1000, 64], 2, 1, 128, "f32", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.3)),
     ([200, 1000, 64], 2, 1, 128, "f32", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.3, gate_dim=32)),
+    # both pooling row splits in one call (whole blocks per thread group from 512 workgroups on: 113 blocks at 72 heads
+    # of 128, 97 at 40 in fp32, 97 at 160 heads of 64)
+    ([8000, 7400, 300, 7168, 7169], 64, 8, 128, "bf16", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.1)),
+    ([14500, 14336, 14337, 300], 64, 8, 128, "bf16", 128, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.1)),
+    ([6500, 200, 6144, 6145], 32, 8, 128, "f32", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.1)),
+    ([6200, 6145, 6144, 100], 128, 32, 64, "bf16", 64, False, dict(mode=seer.TOPK_FIXED, topk_k=4)),
 ]
 
 
