@@ -849,7 +849,7 @@ VarlenMaskOffsets varlen_mask_offsets(const int32_t* cu, int b, int heads, int b
 }
 
 // Scratch rows of the sequences that share one gate launch: bounded, as one
-// launch of this many already fills the GPU (26 sequences of 8192 tokens at 32
+// launch of this many already fills the GPU (25 sequences of 8192 tokens at 32
 // query / 8 KV heads of 128).
 constexpr size_t kPackedGateBytes = (size_t)64 << 20;
 
@@ -984,7 +984,8 @@ size_t seer_gate_varlen_workspace_bytes(const seer_attn_desc* desc, const int32_
     need = std::max(need, gate_layout(&sd, gate, true).total);
     if (packed_gate_class(&sd, gate) != 0) rows += blocks_of(sd.seq_len, gate->block);
   }
-  return std::max(need, std::min(packed_gate_bytes(desc, gate, rows), kPackedGateBytes));
+  if (rows > 0) need = std::max(need, std::min(packed_gate_bytes(desc, gate, rows), kPackedGateBytes));
+  return need;
 }
 
 seer_status seer_gate_varlen(const seer_attn_desc* desc, const int32_t* cu_seqlens_host,

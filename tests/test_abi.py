@@ -408,3 +408,13 @@ def test_varlen_rejects_bad_offsets_and_sizes_the_mask():
     assert L.seer_bsattn_varlen(C.byref(d), good, 96, C.byref(m), 1, 0.0, *args) == seer.ERR_UNSUPPORTED
     assert L.seer_gate_varlen(C.byref(d), good, C.byref(g), FAKE, FAKE, FAKE, FAKE, C.byref(m), None, 0,
                               None) == seer.ERR_WORKSPACE
+
+
+def test_varlen_workspace_of_empty_sequences_reads_no_gate():
+    L = seer.lib()
+    d = _desc(B=2, Hq=4, Hkv=2, S=1)
+    d.seq_len = 0
+    empty = (C.c_int32 * 3)(0, 0, 0)
+    g = _gate()
+    assert L.seer_gate_varlen_workspace_bytes(C.byref(d), empty, C.byref(g)) == 0
+    assert L.seer_gate_varlen_workspace_bytes(C.byref(d), empty, None) == 0
