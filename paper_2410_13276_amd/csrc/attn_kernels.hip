@@ -1857,11 +1857,20 @@ static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count) 
 }
 
 // A sequence joins the packed launch while the K and V of its KV heads fit the
-// phase budget (8192 tokens at 8 KV heads of 128): alone, such a sequence runs
-// one launch over all its heads, which leaves most of the GPU idle; a longer
-// one fills it and keeps its own launches and their order.
-bool attn_packs(const AttnArgs& a, int n_blocks) {
-  return a.bf16 && a.count != nullptr && 4.0 * a.heads_kv * n_blocks * 64.0 * a.head_dim <= kPhaseBudget;
+// phase budget (8192 tokens at 8 KV heads of 128), which the packed order, one
+// sequence after another, does not divide; and while its rows are too few for a
+// launch of their own to be as good: fewer than four rounds of the 1024 workgroups
+// that the GPU holds at head dim 128, three where a length of whole tiles would
+// alone run the plain loop, 4-5% faster per tile than the packed one.  Two equal
+// sequences, prefill alone / packed, us: 4096 rows of whole tiles (32 heads, 8192
+// tokens) 375 / 383; 4092 rows (4 / 1 heads, 65472 tokens) 1188 / 1233, ending
+// inside a tile 1237 / 1237; 3072 rows (12 / 4 heads, 16384 tokens) 317 / 321,
+// ending inside a tile 333 / 325; 3040 rows (32 / 8 heads, 6080 tokens) 167 / 167;
+// 2560 rows (8 / 1 heads, 20480 tokens) 320 / 319, 337 / 324.
+bool attn_packs(const AttnArgs& a, int seq_len) {
+  const int64_t n_blocks = ((int64_t)seq_len + 63) / 64, rows = a.heads_q * n_blocks;
+  return a.bf16 && a.count != nullptr && rows < (seq_len % 64 == 0 ? 3072 : 4096) &&
+         4.0 * a.heads_kv * n_blocks * 64.0 * a.head_dim <= kPhaseBudget;
 }
 
 hipError_t launch_attn_packed(const AttnArgs& a, const PackedSeqs& seqs, hipStream_t s) {

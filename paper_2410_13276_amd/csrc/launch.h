@@ -207,8 +207,8 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t s, int* count = nullptr);
 // options): `a` describes the packed tensors and the packed mask, its seq_len,
 // n_blocks and mask_blocks are the sequences' own.
 hipError_t launch_attn_packed(const AttnArgs& a, const PackedSeqs& seqs, hipStream_t s);
-// Whether a sequence of n_blocks tiles joins such a launch.
-bool attn_packs(const AttnArgs& a, int n_blocks);
+// Whether a sequence of seq_len tokens joins such a launch.
+bool attn_packs(const AttnArgs& a, int seq_len);
 struct F32Shape {
   int groups, halves;
 };

@@ -33,6 +33,10 @@ CASES = [
     ([14500, 14336, 14337, 300], 64, 8, 128, "bf16", 128, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.1)),
     ([6500, 200, 6144, 6145], 32, 8, 128, "f32", 64, False, dict(mode=seer.TOPK_RATIO, topk_ratio=0.1)),
     ([6200, 6145, 6144, 100], 128, 32, 64, "bf16", 64, False, dict(mode=seer.TOPK_FIXED, topk_k=4)),
+    # both sides of the rows that share an attention launch (3072 of whole tiles, 4096 else), and one left by itself
+    ([8175, 8127, 6144, 6080, 6143], 32, 8, 128, "bf16", 64, False, dict(mode=seer.TOPK_FIXED, topk_k=6)),
+    ([33000, 24576, 24512, 300], 8, 1, 128, "bf16", 64, False, dict(mode=seer.TOPK_FIXED, topk_k=6)),
+    ([33000, 0, 300], 8, 1, 128, "bf16", 64, False, dict(mode=seer.TOPK_FIXED, topk_k=6)),
 ]
 
 
