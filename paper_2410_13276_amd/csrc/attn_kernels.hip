@@ -1214,7 +1214,7 @@ void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
   bool none;
   // QS 1: workgroups 16 n + x and 16 n + 8 + x hold the two halves of task 8 n + x (one XCD)
   const int wg = blockIdx.x;
-  const Task t = decode_task(ka.map, QS == 2 ? wg : (wg >> 4) * 8 + (wg & 7), none);
+  const Task t = decode_task(ka.map, QS == 2 ? wg + ka.task_base : (wg >> 4) * 8 + (wg & 7), none);
   if (none) return;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -1698,10 +1698,17 @@ static int kv_heads_per_wg(const AttnArgs& a) {
   return 1;
 }
 
+// A launch holds fewer than 2^32 threads: calls of more rows than 2^23 workgroups of
+// 256 threads run as several launches.
 template <int D>
-static void launch_f32(const LaunchArgs<false>& ka, int qs, unsigned total, hipStream_t s, int* count, bool sparse) {
-  if (ka.a.f32_groups == 1) SEER_LAUNCH((attn_fwd_f32_kernel<D, 1, 2>), dim3(total), dim3(256), s, count, ka, (int)sparse);
-  else if (qs == 2) SEER_LAUNCH((attn_fwd_f32_kernel<D, 2, 2>), dim3(total), dim3(512), s, count, ka, (int)sparse);
+static void launch_f32(LaunchArgs<false> ka, int qs, unsigned total, hipStream_t s, int* count, bool sparse) {
+  constexpr unsigned kMost = 1u << 23;
+  if (ka.a.f32_groups == 1) {
+    for (unsigned t0 = 0; t0 < total; t0 += kMost) {
+      ka.task_base = (int)t0;
+      SEER_LAUNCH((attn_fwd_f32_kernel<D, 1, 2>), dim3(std::min(total - t0, kMost)), dim3(256), s, count, ka, (int)sparse);
+    }
+  } else if (qs == 2) SEER_LAUNCH((attn_fwd_f32_kernel<D, 2, 2>), dim3(total), dim3(512), s, count, ka, (int)sparse);
   else SEER_LAUNCH((attn_fwd_f32_kernel<D, 2, 1>), dim3(2 * total), dim3(256), s, count, ka, (int)sparse);
 }
 

@@ -52,3 +52,20 @@ def test_f32_sparse_and_dense(B, Hq, Hkv, S, D, causal):
     ws = torch.empty(seer.attn_gt_workspace_bytes(qd, kd, vd, 1), dtype=torch.uint8, device="cuda")
     o1, _, gt1 = seer.attn_gt(qd, kd, vd, causal=causal, workspace=ws)  # one KV group per launch
     assert torch.equal(og, od) and torch.equal(o1, od) and torch.equal(gt1, gt)
+
+
+def test_more_rows_than_one_launch_holds():
+    """2^24 + 64 rows of one token (a launch holds fewer than 2^32 threads, 256 a row): O = V exactly."""
+    B, Hq, D = (1 << 18) + 1, 64, 64
+    print(f"[f32] {B} x {Hq} rows of one token", flush=True)
+    q = torch.ones(1, 1, 1, D, device="cuda").expand(B, Hq, 1, D)
+    k = torch.ones(B, 1, 1, D, device="cuda")
+    v = torch.arange(B, dtype=torch.float32, device="cuda").view(B, 1, 1, 1).expand(B, 1, 1, D).contiguous()
+    o = torch.full((B, Hq, 1, D), -1.0, device="cuda")
+    seer.dense_attn(q, k, v, out=o)
+    assert bool((o == v).all())
+    mask = seer.BlockMask(count=torch.ones(B, Hq, 1, dtype=torch.int32, device="cuda"),
+                          idx=torch.zeros(B, Hq, 1, 1, dtype=torch.uint16, device="cuda"))
+    o.fill_(-1.0)
+    seer.bsattn(q, k, v, mask, out=o)
+    assert bool((o == v).all())
