@@ -78,17 +78,27 @@ __device__ __forceinline__ int divide(const Divisor& v, int u) {
 struct TaskMap {
   int groups, nb;  // groups = batch * heads_kv
   int rsh;         // log2 of the XCDs per group, R
-  int gpp;         // groups per phase (R * gpp == 8)
+  int gpp;         // groups per phase (R * gpp == 8); 0: every head's rows interleaved
   int total;       // workgroups of all phases
   Divisor hkv;     // KV heads
-  Divisor G;       // query heads per group
-  Divisor tpp;     // tasks per XCD per phase = ceil(nb / R) * G
+  Divisor G;       // query heads per group (interleaved: query heads)
+  Divisor tpp;     // tasks per XCD per phase = ceil(nb / R) * G (interleaved: heads of all batches)
 };
 
 // A workgroup without a task decodes to row 0 of an existing head with `none`
 // set: it may read its task's inputs before it ends.
 __device__ __forceinline__ Task decode_task(const TaskMap& m, int wg, bool& none) {
   Task t;
+  t.p = 0;
+  if (m.gpp == 0) {
+    const int nu = divide(m.tpp, wg);
+    const int rem = wg - nu * (int)m.tpp.d;
+    t.b = divide(m.G, rem);
+    t.h = rem - t.b * (int)m.G.d;
+    none = nu >= m.nb;
+    t.i = max(m.nb - 1 - nu, 0);
+    return t;
+  }
   const int x = wg & 7;
   const int u = wg >> 3;
   const int ph = divide(m.tpp, u);
@@ -102,7 +112,6 @@ __device__ __forceinline__ Task decode_task(const TaskMap& m, int wg, bool& none
   t.i = max(i, 0);
   t.b = divide(m.hkv, min(slot, m.groups - 1));
   t.h = (min(slot, m.groups - 1) - t.b * (int)m.hkv.d) * (int)m.G.d + hh;
-  t.p = 0;
   return t;
 }
 
@@ -1518,34 +1527,93 @@ __global__ __launch_bounds__(256) void split_bounds_kernel(AttnArgs a) {
 // groups' unequal work no longer leaves half the XCDs idle at the end; 8k and
 // 32k shapes (4 and 16 MiB per group) ran the same with budgets of 32 and 64 MiB,
 // and slower with 16 or less.
-// Rows of a mask shared by each group (mask_kv) can differ widely in length from
-// group to group (thresholds per KV head), which idles XCDs where a phase gives
-// each group some of them.  There a block count that R does not divide goes one
-// group at a time: 32698 tokens, 28 / 4 heads, shares of 5-40% per group, a
-// prefill 2.31 -> 1.95 ms (2.11 with the rows of all groups interleaved).
-// (Masks per head average over a group's heads; one group at a time measured
-// 0.95-1.05x there, the most a call lost to the interleaved rows 5.6%: 19000
-// tokens, 12 / 4 heads, shares of 5-40% per head, 368 -> 390 us, 412 one group
-// at a time, against gains of 1.1-1.6x on most lengths.)
+// Block counts that fit the phases exactly run so whatever the call; the others
+// have a choice, and need it: a phase order leaves XCDs idle where a call has few
+// rows (every phase ends with short rows while the next one's long rows wait) and
+// where the groups of a phase have unequal work.  See interleaves() and make_map().
 constexpr double kPhaseBudget = 32.0 * 1024.0 * 1024.0;
 
 static Divisor divisor(int d) {
   return Divisor{(uint32_t)d, (uint32_t)std::min<uint64_t>((1ull << 32) / (uint32_t)d, 0xFFFFFFFFull)};
 }
 
-static TaskMap make_map(const AttnArgs& a) {
-  TaskMap m;
+static double kv_bytes(const AttnArgs& a) {
+  return 2.0 * a.n_blocks * 64.0 * a.head_dim * (a.bf16 ? 2 : 4);
+}
+
+// Whether some allowed number of groups per phase divides the groups, and its XCDs
+// per group the blocks.
+static bool phases_divide(const AttnArgs& a) {
+  for (int gpp = 8; gpp >= 1; gpp /= 2)
+    if (a.batch * a.heads_kv % gpp == 0 && a.n_blocks % (8 / gpp) == 0 && (gpp == 1 || gpp * kv_bytes(a) <= kPhaseBudget))
+      return true;
+  return false;
+}
+
+// Whether a call whose block count fits no phase exactly runs every head's rows
+// interleaved, heaviest first over the whole launch (up to 8 heads: one per XCD).
+// That order balances best and shares K/V least, so it is the better one
+//  - for few rows; the fewer heads share a group, the more rows are few.  Sparse, us,
+//    a share of 20% for every head / 5-40% shuffled over the heads / ascending,
+//    interleaved against phases: 16 / 16 heads, 141 blocks 98 / 137 / - against 115 / 150; 8 / 8
+//    heads, 297 blocks 184 / 262 / - against 217 / 323; 12 / 4 heads, 205 blocks 153
+//    / 191 / 181 against 140 / 180 / 224; with three rounds of workgroups and
+//    more the phases win at three and more heads per group (28 / 4 heads, 297 blocks
+//    819 / 1116 / 999 against 620 / 767 / 770), with five at two and fewer (32 / 32
+//    heads, 205 blocks 435 / 533 against 403 / 467);
+//  - for up to 8 heads in groups of at most two, each of which has an XCD's L2 to
+//    itself (8 / 8 heads, 2188 blocks 9.6 / 14.8 against 11.5 / 12.8 ms);
+//  - for dense rows in fp32 or with at most two workgroups per group: equal work,
+//    nothing to balance (16 / 16 heads, 297 blocks 1485 against 1616; 32 / 8 heads,
+//    782 blocks 17.7 against 18.2 ms; three per group, 12 / 4 heads, 297 blocks 1157
+//    against 1120, in fp32, 313 blocks, 9353 against 9715).
+// fp32 holds half the workgroups at once, and shares K/V less (the matrix core
+// bounds it): 8 / 8 heads, 205 blocks 651 against 746; 12 / 4 heads, 141 blocks 492
+// against 527, 205 blocks 959 against 954.
+// No order is the best one for every mask: where the phases are taken, 24 / 8 heads and
+// 141 blocks lose 6% with ascending shares (185 against 175; 145 / 178 against 147 /
+// 181) and 16 / 8 heads and 511 blocks 6% with equal shares of a mask per group (937
+// against 887; 1085 against 1427 with unequal ones).
+// nh: query heads per workgroup.
+static bool interleaves(const AttnArgs& a, int nh) {
+  if (a.batch * a.heads_kv == 1 || phases_divide(a)) return false;  // (one group: its heads' rows are adjacent anyway)
+  const int heads = a.batch * a.heads_q, G = a.heads_q / a.heads_kv;
+  if (!a.count && (G / nh <= 2 || !a.bf16)) return true;
+  const int64_t rows = (int64_t)heads * a.n_blocks;
+  if (G <= 2) return heads <= 8 || rows < (a.bf16 && a.head_dim == 64 ? 7680 : 5120);
+  return rows < (!a.bf16 ? 2048 : a.head_dim == 64 ? 4608 : 3072);
+}
+
+// Otherwise such a call runs in rounded-up phases.  Sparse rows can differ from
+// group to group (thresholds per head or KV group), so a phase holds at most half of
+// the groups (28 / 4 heads, 205 blocks, two groups against four: 316 / 366 / 391
+// against 312 / 361 / 484 us, shares as above; 14 / 2 heads, 297 blocks, one against
+// two: 316 / 383 / 368 against 310 / 366 / 455), and one where the mask is each
+// group's own (28 / 4 heads, 511 blocks, equal shares / 5-40% shuffled: 1730 / 1914
+// us, the interleaved rows 2853 / 3453; 32 / 8 heads, 297 blocks 640 / 709, two
+// groups 632 / 750).  (At counts that fit the phases, one group at a time takes 1816
+// us against 2194 for unequal shared shares, 28 / 4 heads and 512 blocks, but 203
+// against 193 for equal ones, 12 / 4 heads and 256 blocks; they keep their phases.)
+static TaskMap make_map(const AttnArgs& a, int nh) {
+  TaskMap m{};
   m.groups = a.batch * a.heads_kv;
   m.nb = a.n_blocks;
-  const int G = a.heads_q / a.heads_kv;
+  const int slots = a.heads_q / nh;  // workgroups per batch and query block
+  if (interleaves(a, nh)) {
+    m.G = divisor(slots);
+    m.tpp = divisor(a.batch * slots);
+    m.total = (int)(((int64_t)a.batch * slots * a.n_blocks + 7) / 8 * 8);
+    return m;
+  }
+  const int G = slots / a.heads_kv;
   m.hkv = divisor(a.heads_kv);
   m.G = divisor(G);
-  const double kv_bytes = 2.0 * a.n_blocks * 64.0 * a.head_dim * (a.bf16 ? 2 : 4);
+  const bool divide = phases_divide(a);
   int64_t fewest = INT64_MAX;
   for (int rsh = 0; rsh <= 3; ++rsh) {
     const int gpp = 8 >> rsh, R = 1 << rsh;
-    if (gpp > 1 && gpp * kv_bytes > kPhaseBudget) continue;
-    if (gpp > 1 && a.count && a.mask_kv && a.n_blocks % R != 0) continue;  // see above
+    if (gpp > 1 && gpp * kv_bytes(a) > kPhaseBudget) continue;
+    if (gpp > 1 && a.count && !divide && (a.mask_kv || 2 * gpp > m.groups)) continue;
     const int tpp = ((a.n_blocks + R - 1) / R) * G;
     const int64_t total = (int64_t)((m.groups + gpp - 1) / gpp) * 8 * tpp;
     if (total >= fewest) continue;
@@ -1558,9 +1626,17 @@ static TaskMap make_map(const AttnArgs& a) {
   return m;
 }
 
-// Whether a phase holds a single group because its K and V fill the budget.
-static bool group_fills_phase(const AttnArgs& a) {
-  return make_map(a).gpp == 1 && 4.0 * a.n_blocks * 64.0 * a.head_dim * (a.bf16 ? 2 : 4) > kPhaseBudget;
+// Whether the groups launch one after another: each fills a phase by itself, and its
+// rows fill the GPU several times over (a launch waits for the last row of the one
+// before it).  Measured, one launch against one per group: sparse, 8 / 8 heads, 640
+// blocks 1022 against 1500 us; 12 / 4 heads, 640 blocks (1920 rows a group) 1129
+// against 1204; 32 / 8 heads, 782 blocks (3128) 4712 against 4796, 1024 blocks (4096) 7574
+// against 7807; 12 / 4 heads, 2048 blocks (6144) 12756 against 12237.  Dense: 16 / 16
+// heads, 1024 blocks 19.6 against 23.0 ms, 2048 blocks 78.2 against 68.4; 16 / 8 heads,
+// 1024 blocks (2048 rows) 15.3 against 15.3.
+static bool groups_launch_alone(const AttnArgs& a, int nh) {
+  const int64_t rows = (int64_t)a.heads_q / a.heads_kv * a.n_blocks;
+  return rows >= (a.count ? 4096 : 2048) && make_map(a, nh).gpp == 1 && 2 * kv_bytes(a) > kPhaseBudget;
 }
 
 }  // namespace
@@ -1647,13 +1723,29 @@ static hipError_t launch_split(const LaunchArgs<false>& ka, bool sparse, hipStre
 
 static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count);
 
+// Query heads per workgroup for rows shared by the query heads of a KV group
+// (a mask shared by the group, or dense rows): the largest of 4, 2 that divides
+// the group and is at most a.heads_per_wg (the option's cap, 2 by default),
+// else 1.  Measured at 131072 tokens, 32 query / 8 KV heads, TopK 0.1: per-head
+// rows 17.3 ms; shared rows with 1, 2 and 4 heads per workgroup 14.3, 13.0 and
+// 13.1 ms (two 4-wavefront workgroups per CU keep their phases independent;
+// one 8-wavefront workgroup moves in lockstep).
+static int kv_heads_per_wg(const AttnArgs& a) {
+  const bool shared_rows = a.count ? a.mask_kv : true;
+  if (!shared_rows || !a.bf16 || a.split_w > 0) return 1;
+  const int G = a.heads_q / a.heads_kv;
+  for (int nh = 4; nh >= 2; nh /= 2)
+    if (nh <= a.heads_per_wg && G % nh == 0) return nh;
+  return 1;
+}
+
 // One launch per KV group when a phase of the task order holds a single group
 // (its K and V alone fill the phase's cache budget): the launch boundary keeps
-// every XCD on the same group's K and V.  Measured at 131072 tokens (sparse):
-// 8 launches 17.8 ms, one launch 18.1 ms.  Not for the split or pooling modes.
+// every XCD on the same group's K and V (groups_launch_alone).  Not for the split or
+// pooling modes.
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s, int* count) {
   const int groups = a.batch * a.heads_kv;
-  if (a.split_w > 0 || a.gt != nullptr || groups <= 1 || !group_fills_phase(a))
+  if (a.split_w > 0 || a.gt != nullptr || groups <= 1 || !groups_launch_alone(a, kv_heads_per_wg(a)))
     return launch_attn_one(a, s, count);
   const int G = a.heads_q / a.heads_kv;
   const int64_t es = a.bf16 ? 2 : 4;
@@ -1680,22 +1772,6 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t s, int* count) {
       if (e != hipSuccess) return e;
     }
   return hipSuccess;
-}
-
-// Query heads per workgroup for rows shared by the query heads of a KV group
-// (a mask shared by the group, or dense rows): the largest of 4, 2 that divides
-// the group and is at most a.heads_per_wg (the option's cap, 2 by default),
-// else 1.  Measured at 131072 tokens, 32 query / 8 KV heads, TopK 0.1: per-head
-// rows 17.3 ms; shared rows with 1, 2 and 4 heads per workgroup 14.3, 13.0 and
-// 13.1 ms (two 4-wavefront workgroups per CU keep their phases independent;
-// one 8-wavefront workgroup moves in lockstep).
-static int kv_heads_per_wg(const AttnArgs& a) {
-  const bool shared_rows = a.count ? a.mask_kv : true;
-  if (!shared_rows || !a.bf16 || a.split_w > 0) return 1;
-  const int G = a.heads_q / a.heads_kv;
-  for (int nh = 4; nh >= 2; nh /= 2)
-    if (nh <= a.heads_per_wg && G % nh == 0) return nh;
-  return 1;
 }
 
 // A launch holds fewer than 2^32 threads: calls of more rows than 2^23 workgroups of
@@ -1762,9 +1838,7 @@ static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count) 
   const int nh = kv_heads_per_wg(a);
   const auto done = [&]() { return count ? hipSuccess : hipGetLastError(); };
   if (nh > 1) {  // tasks over head slots of nh heads: the task order sees heads_q / nh heads
-    AttnArgs v = a;
-    v.heads_q = a.heads_q / nh;
-    ka.map = make_map(v);
+    ka.map = make_map(a, nh);
     const int64_t total = ka.map.total;
     if (total == 0) return hipSuccess;
     ka.split = SplitMap{a.heads_q, a.heads_kv, a.n_blocks, 0, 0, 0, 0, 1};
@@ -1781,7 +1855,7 @@ static hipError_t launch_attn_one(const AttnArgs& a, hipStream_t s, int* count) 
     else return hipErrorInvalidValue;
     return done();
   }
-  ka.map = make_map(a);
+  ka.map = make_map(a, 1);
   ka.split = SplitMap{a.heads_q, a.heads_kv, a.n_blocks, a.split_w, a.split_parts, 0, 0, 1};
   if (a.split_w > 0) {
     const int64_t G = a.heads_q / a.heads_kv, P = a.split_parts, w = a.split_w;

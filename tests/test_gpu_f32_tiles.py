@@ -18,7 +18,7 @@ seer = pytest.importorskip("paper_2410_13276_amd")
 
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("B,Hq,Hkv,S,D", [(1, 2, 1, 1, 64), (1, 2, 1, 130, 64), (1, 2, 1, 1000, 64), (1, 16, 4, 1024, 64),
-                                          (1, 16, 4, 1025, 64), (2, 24, 8, 1024, 64), (1, 49, 7, 1000, 64),
+                                          (1, 16, 4, 1025, 64), (1, 6, 2, 300, 64), (2, 24, 8, 1024, 64), (1, 49, 7, 1000, 64),
                                           (1, 2, 1, 65, 128), (1, 16, 4, 1024, 128), (1, 16, 4, 1030, 128),
                                           (1, 26, 2, 1900, 128)])
 def test_f32_sparse_and_dense(B, Hq, Hkv, S, D, causal):

@@ -11,9 +11,12 @@ seer = pytest.importorskip("paper_2410_13276_amd")
 
 
 # 1 and 2 blocks with odd group counts (phases rounded up over groups), block counts around 8, and K + V beyond
-# the 32 MiB of a phase (261 and 523 blocks: 4 and 2 groups per phase at 8 groups; 1021: one launch per group)
+# the 32 MiB of a phase (261 and 523 blocks; 205, 261: half of the groups per phase; 611 at 7 heads a group: one
+# launch per group); interleaved rows: 1, 9 and 10 blocks, 1021 and 523 with few heads a group
 @pytest.mark.parametrize("B,Hq,Hkv,seq", [(1, 1, 1, 1), (9, 2, 1, 100), (3, 6, 3, 64), (5, 3, 3, 449), (1, 4, 2, 577),
-                                          (2, 14, 2, 1001), (1, 16, 8, 16700), (1, 8, 8, 33409), (1, 4, 2, 65300)])
+                                          (2, 14, 2, 1001), (1, 16, 8, 16700), (1, 8, 8, 33409), (1, 4, 2, 65300),
+                                          (1, 12, 12, 577), (3, 2, 2, 640), (2, 16, 4, 13100), (1, 16, 4, 16700),
+                                          (1, 14, 2, 39050)])
 def test_every_row_once(B, Hq, Hkv, seq):
     print(f"[task order] {B} {Hq}/{Hkv} {seq}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(seq)
@@ -61,3 +64,12 @@ def test_every_row_of_a_shared_mask_once(Hq, Hkv, seq):
         qs = q[:, hs].contiguous()
         o1, _ = seer.bsattn(qs, k[:, g:g + 1], v[:, g:g + 1], m)
         assert torch.equal(o[:, hs].view(torch.int16), o1.view(torch.int16))
+
+
+@pytest.mark.parametrize("Hq,Hkv,seq,launches", [(8, 8, 39050, 1), (8, 8, 40960, 1), (12, 4, 50001, 1), (14, 2, 39050, 2),
+                                                 (28, 4, 65536, 4)])
+def test_groups_of_few_rows_share_a_launch(Hq, Hkv, seq, launches):
+    """One launch per KV group only from 4096 rows a group on."""
+    q, k = (torch.empty(1, h, seq, 128, dtype=torch.bfloat16, device="cuda") for h in (Hq, Hkv))
+    mask = seer.alloc_mask(1, Hq, seq)
+    assert seer.attn_launches(q, k, k, mask) == launches
