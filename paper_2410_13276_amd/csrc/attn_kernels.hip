@@ -1960,6 +1960,7 @@ hipError_t launch_attn_packed(const AttnArgs& a, const PackedSeqs& seqs, hipStre
   ka.a = a;
   ka.seqs = seqs;
   const int nh = kv_heads_per_wg(a);
+  if (nh > 2) return hipErrorInvalidValue;  // (the option's default is 2, and these calls have no options)
   const int slots = a.heads_q / nh;
   ka.map = TaskMap{};
   ka.map.hkv = divisor(a.heads_kv);
