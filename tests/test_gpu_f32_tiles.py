@@ -69,3 +69,46 @@ def test_more_rows_than_one_launch_holds():
     o.fill_(-1.0)
     seer.bsattn(q, k, v, mask, out=o)
     assert bool((o == v).all())
+
+
+# 6 and 126 rows (a workgroup per query half), 378 (two tile groups), 1032 (one)
+@pytest.mark.parametrize("B,S", [(3, 130), (9, 448), (27, 448), (86, 381)])
+def test_scores_beyond_the_finite(B, S):
+    """+inf and NaN scores make the rows that see them NaN; -inf scores and the type's lowest are weights like
+    any other beside an ordinary one (a row of nothing but -inf is empty: O = 0, LSE = -inf), wherever in the tiles, key halves and tile
+    groups they stand.  Against softmax in 64 bits."""
+    print(f"[f32] non-finite scores {B} {S}", flush=True)
+    D, low = 64, -3.0e38
+    gen = torch.Generator().manual_seed(S)
+    s = torch.randn(B, S, generator=gen) * 3
+    inf = float("inf")
+    kind = torch.arange(B) % 3
+    s[kind == 0, S // 2] = inf          # rows from S // 2 on are NaN
+    s[kind == 0, :40] = -inf            # rows before 40 are empty, a whole key half
+    s[kind == 1, S // 3] = float("nan")
+    s[kind == 1, 1:S // 4] = low        # (key 0 stays: a row's largest score has to be one that its own rounding times
+    s[kind == 2, :] = -inf              # the scale, 2^-24 of it, does not swamp)
+    s[kind == 2, S - 3] = 1.0           # the only key of the last rows
+    q = torch.zeros(B, 1, S, D)
+    q[..., 0] = 1.0
+    k = torch.zeros(B, 1, S, D)
+    k[:, 0, :, 0] = s
+    v = torch.randn(B, 1, S, D, generator=gen)
+    w = (s.double() / 8).view(B, 1, S).expand(B, S, S)
+    w = w.masked_fill(~torch.ones(S, S, dtype=torch.bool).tril(), -inf)
+    empty = (w == -inf).all(-1)
+    p = torch.softmax(w, -1)
+    ref = torch.where(empty.unsqueeze(-1), 0.0, p @ v[:, 0].double())
+    # (a zero weight times a finite value: NaN comes from the scores alone)
+    bad = torch.isnan(p).any(-1) & ~empty
+    o, lse = seer.dense_attn(q.cuda(), k.cuda(), v.cuda(), want_lse=True)
+    nb = -(-S // 64)
+    full = torch.ones(B, 1, nb, nb, dtype=torch.uint8, device="cuda").tril()
+    o2, _ = seer.bsattn(q.cuda(), k.cuda(), v.cuda(), seer.mask_from_dense(full))
+    for out in (o[:, 0].cpu(), o2[:, 0].cpu()):
+        assert torch.equal(torch.isnan(out).any(-1), bad) and bool(torch.isnan(out[bad]).all())
+        assert float((out[~bad].double() - ref[~bad]).abs().max()) <= ATOL_F32
+    got, want = lse[:, 0].cpu(), torch.logsumexp(w, -1)
+    assert bool((got[empty] == -inf).all())
+    fin = ~bad & ~empty
+    assert bool(((got[fin] - want[fin]).abs() <= 1e-4 * want[fin].abs().clamp(min=1)).all())

@@ -1,8 +1,10 @@
 """Packed batches whose short sequences share launches: every count, index list
 and output equals, bit for bit, the calls on the sequences one by one (views of
 the same tensors), over sequence counts around the 64 of one launch, sequences
-on both sides of the sharing limits (128 blocks in the gate, 32 MiB of K and V
-in attention), workspaces that hold one or all of them, and every option."""
+on both sides of the sharing limits (128 blocks and the pooling's row split in the
+gate; rows, and 32 MiB of K and V, in attention), workspaces that hold one or all of
+them, per-head and shared masks and weights, thresholds per head, and attention
+without causality over masks that reach a partial last tile."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -81,3 +83,64 @@ def test_packed_equals_separate_calls(case):
             assert torch.equal(mask.dense[i0:i0 + mask.heads * nb * nb].view_as(m.dense[0]), m.dense[0])
             assert torch.equal(out[cu[b]:cu[b + 1]].permute(1, 0, 2), o1[0])
             assert torch.equal(lse[Hq * cu[b]:Hq * cu[b + 1]].view(Hq, n), l1[0])
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,dg,kw", [(6, 2, 64, 64, dict(w_per_head=False)), (32, 8, 128, 32, dict(w_per_head=False)),
+                                            (8, 2, 128, 128, dict(keep_first=False, keep_diag=False))])
+def test_packed_gate_options(Hq, Hkv, D, dg, kw):
+    """Shared weights and thresholds per head through the shared gate launches."""
+    print(f"[packed] options {Hq}/{Hkv} {D} {kw}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(Hq)
+    cu = [0, 700, 700, 2765, 2766, 6900]
+    q, k = (torch.randn(cu[-1], h, D, generator=gen, device="cuda").bfloat16() for h in (Hq, Hkv))
+    heads = kw.get("w_per_head", True)
+    wq = torch.randn(*([Hq] if heads else []), D, dg, generator=gen, device="cuda") / dg ** 0.5
+    wk = torch.randn(*([Hkv] if heads else []), 3 * D, dg, generator=gen, device="cuda") / dg ** 0.5
+    kw = dict(kw, mode=seer.THRESHOLD, head_thresholds=torch.linspace(0.01, 0.2, Hq, device="cuda"))
+    mask = seer.gate_varlen(q, k, wq, wk, cu, **kw)
+    for b in range(len(cu) - 1):
+        if cu[b + 1] > cu[b]:
+            qb, kb = (t[cu[b]:cu[b + 1]].permute(1, 0, 2).unsqueeze(0) for t in (q, k))
+            m = seer.gate(qb, kb, wq, wk, **kw)
+            cnt, idx = mask.sequence(b)
+            keep = torch.arange(cnt.shape[1], device="cuda") < cnt.unsqueeze(-1)
+            assert torch.equal(cnt, m.count[0])
+            assert torch.equal(idx.masked_fill(~keep, 0), m.idx[0].view(torch.int16).masked_fill(~keep, 0))
+            assert len(set(cnt[:, -1].tolist())) > 1 or cnt.shape[1] == 1  # the thresholds differ
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,block,shared", [(4, 2, 128, 64, False), (6, 2, 64, 64, False), (4, 2, 64, 64, True),
+                                                   (4, 1, 128, 128, False)])
+def test_packed_attention_without_causality(Hq, Hkv, D, block, shared):
+    print(f"[packed] non-causal {Hq}/{Hkv} {D} {block} {shared}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(D + block)
+    cu = [0, 500, 1012, 1013, 1013, 1790, 1918]  # partial last tiles of 52, 1 and 9 tokens, whole ones, an empty sequence
+    q, k, v = (torch.randn(cu[-1], h, D, generator=gen, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    mask = seer.alloc_varlen_mask(q, k, cu, block, shared)
+    H = Hkv if shared else Hq
+    singles = []
+    for b in range(len(cu) - 1):
+        n = cu[b + 1] - cu[b]
+        if n == 0:
+            continue
+        nb = -(-n // block)
+        dense = (torch.rand(1, H, nb, nb, generator=gen, device="cuda") < 0.5).to(torch.uint8)
+        dense[:, :, 0, -1] = 1  # the partial tile, far above the diagonal
+        cnt, idx = mask.sequence(b)
+        cnt.copy_(dense[0].sum(-1))
+        idx.copy_(torch.argsort(dense[0], dim=-1, descending=True, stable=True).to(torch.int16))
+        m = seer.BlockMask(count=cnt.clone().unsqueeze(0), idx=idx.clone().unsqueeze(0), block=block, kv_shared=shared)
+        qb, kb, vb = (t[cu[b]:cu[b + 1]].permute(1, 0, 2).unsqueeze(0) for t in (q, k, v))
+        singles.append((b, n, seer.bsattn(qb, kb, vb, m, causal=False, want_lse=True)))
+        rows = torch.arange(n, device="cuda")[:, None] // block, torch.arange(n, device="cuda")[None] // block
+        on = dense[0][:, rows[0], rows[1]].repeat_interleave(Hq // H, 0).bool()
+        s = (qb[0].float() @ kb[0].float().repeat_interleave(Hq // Hkv, 0).transpose(1, 2)) / D ** 0.5
+        p = torch.softmax(s.masked_fill(~on, float("-inf")), -1).nan_to_num(0.0)
+        ref = p @ vb[0].float().repeat_interleave(Hq // Hkv, 0)
+        assert float((singles[-1][2][0][0].float() - ref).abs().max()) <= 2e-2  # (the bf16 bar of the other tests)
+    out = torch.full_like(q, float("nan"))
+    lse = torch.full((Hq * cu[-1],), float("nan"), device="cuda")
+    seer.bsattn_varlen(q, k, v, cu, mask, causal=False, out=out, lse=lse)
+    for b, n, (o1, l1) in singles:
+        assert torch.equal(out[cu[b]:cu[b + 1]].permute(1, 0, 2), o1[0])
+        assert torch.equal(lse[Hq * cu[b]:Hq * cu[b + 1]].view(Hq, n), l1[0])
