@@ -253,7 +253,10 @@ size_t seer_gate_noalloc_max_bytes(void);
  * log-sum-exp of each query's scaled scores.  A row with no active block
  * yields O = 0 and LSE = -inf.  When causal, list entries j > i end the row;
  * entries j >= nb always end it, and count is clamped to nb, so a malformed
- * mask cannot make the kernel read out of bounds.
+ * mask cannot make the kernel read out of bounds.  A bf16 row's result depends on
+ * its own inputs alone; an fp32 row's sums are formed in an order that follows the
+ * call's number of (batch, head, query block) rows (up to 256, up to 768, more), so
+ * the same sequence in a larger batch can differ by rounding (about 1e-7).
  * Unsupported: block not in {64, 128}, head_dim not in {64, 128}.
  */
 seer_status seer_bsattn(const seer_attn_desc* desc, int32_t block, const seer_block_mask* mask,

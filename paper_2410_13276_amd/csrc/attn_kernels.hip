@@ -541,8 +541,13 @@ constexpr int kListWhole = 2048;
 // dim 128 needs 210-230 registers per lane: two.  Head dim 64 has as much
 // softmax work per tile but half the MFMA work, and fits 168 registers: three
 // (4 x 16 heads of 4000 tokens, 12 blocks per row: attention 88 -> 79 us; 43161
-// tokens, 28 blocks: prefill 471 -> 439 us; launches that do not fill the GPU
-// within 1%; four would spill: 88 -> 120 us).  The split kernels need up to 196.
+// tokens, 28 blocks: prefill 471 -> 439 us; up to 1024 rows within 2%; four would
+// spill: 88 -> 120 us).  Between the 1024 workgroups held at two and the 1536 at
+// three, and up to 2048, long rows can lose what short ones gain: 12 / 4 heads, 8192
+// tokens, 40% of the blocks 65 -> 72 us, none but the diagonal 15 -> 11; 8 / 8 heads,
+// 16001 tokens dense 314 -> 355, 10% of the blocks 52 -> 52; 32 / 8 heads, 4000 tokens
+// 40% 50 -> 48.  (LDS that keeps such launches at two gains back only the dense ones,
+// 357 -> 338, and costs short rows 10-50%.)  The split kernels need up to 196.
 constexpr int waves_per_simd(int head_dim, bool split) { return head_dim == 64 && !split ? 3 : 2; }
 
 // Pipeline per key tile n (one K and one V buffer, two barriers):
@@ -1365,6 +1370,7 @@ void attn_fwd_f32_kernel(LaunchArgs<false> ka, int sparse) {
 #pragma unroll
           for (int e = 0; e < 16; ++e) acc[dt][e] *= alpha;
       }
+      // (v_exp_f32: weights below 2^-126 of the maximum are zero)
       float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
@@ -1664,7 +1670,12 @@ int64_t split_slots_per_head(int n_blocks, int w) {
 // -> 194).  Up to 768, two tile groups balance the rows better over one round of
 // workgroups (512 rows 213 -> 162 / 392 -> 302); from 1024 on the workgroups do
 // that themselves, and two per CU hide each other's barriers (2048 rows: 559
-// against 611 / 1080 against 1142).
+// against 611 / 1080 against 1142).  Rows of a single tile have nothing to share (the
+// diagonal alone, 752 rows of 64: 18 us with one group, 27 with two); from three tiles
+// a row on, on average, two are faster.
+//
+// A row's sums are formed in the order of its groups, so an fp32 result can differ in
+// rounding (1e-7) between a call and the same sequence in a larger one.
 F32Shape f32_shape(int64_t rows) {
   return F32Shape{rows <= 768 ? 2 : 1, rows <= 256 ? 1 : 2};
 }
@@ -1807,7 +1818,7 @@ static void launch_nh_d(const LaunchArgs<false>& ka, int nh, bool sparse, bool r
 }
 
 // Sparse rows of long sequences launch in batches of exactly the workgroups the
-// GPU holds at once (4 per CU), so that the rows of a batch start together and
+// GPU holds at once (4 per CU at head dim 128, 6 at 64), so that the rows of a batch start together and
 // walk their ascending lists roughly in step: concurrent rows then share more
 // of their K/V tiles in L2.  Within a batch the order is the usual one (task
 // ids continue across batches), so every output is unchanged.  Only the

@@ -128,6 +128,8 @@ __device__ __forceinline__ void pool_proj_head(const T* __restrict__ x, int64_t 
   // whose few workgroups cannot hide it (2048 tokens, 32 query / 8 KV heads of
   // 128: 20.6 -> 15.4 us; 8192: 31.9 -> 26.9; 64 ahead spill), and some of a
   // long one (50001: 119 -> 114, 131072: 297 -> 288; 32 ahead no faster).
+  // (RS is the single sequence's: a packed launch of RS 4 takes a short launch's
+  // settings also where it fills the GPU, at 107-167 registers against 74-80.)
   constexpr int kAhead = RS > 1 ? 32 : 16;
   static_assert(WIDTH % kAhead == 0, "the weights are read in whole steps");
   float wn[kAhead];
